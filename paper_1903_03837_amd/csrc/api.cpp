@@ -193,8 +193,8 @@ void pack_trace(lp::TraceParams& T, const lf_volume* v, const lf_medium* e, cons
     T.vol = v->data;  // replaced by the workspace's halo-brick copy
     T.nx = v->nx;
     T.ny = v->ny;
-    T.brick_row = 64 * lp::halo_bricks(v->nx);
-    T.brick_slab = 64 * lp::halo_bricks(v->nx) * lp::halo_bricks(v->ny);
+    T.nbx = lp::halo_bricks(v->nx);
+    T.nby = lp::halo_bricks(v->ny);
     const int n[3] = {v->nx, v->ny, v->nz};
     for (int a = 0; a < 3; ++a) {
         const double ext = (double)v->box_max[a] - (double)v->box_min[a];
