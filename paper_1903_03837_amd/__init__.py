@@ -217,7 +217,7 @@ class GenParams:
     grid: int = 0                            # majorant grid cells per axis (0: one global majorant)
     surface: int = 0                         # 1: isosurface variant at raw value iso
     iso: float = 0.0
-    waves_per_simd: int = 0                  # forward tracer's register budget: 0 (library's choice), 3 or 4
+    waves_per_simd: int = 0                  # 0, 3 or 4: no effect (the tracer always budgets for 4)
 
     @property
     def rows(self) -> int:

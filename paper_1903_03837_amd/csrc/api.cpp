@@ -189,7 +189,6 @@ int check_light(const lf_light* l) {
 void pack_trace(lp::TraceParams& T, const lf_volume* v, const lf_medium* e, const lf_medium* s,
                 const lf_light* l, const lf_gen_params* p) {
     std::memset(&T, 0, sizeof(T));
-    T.waves = p->waves_per_simd == 3 ? 3 : 4;
     T.vol = v->data;  // replaced by the workspace's halo-brick copy
     T.nx = v->nx;
     T.ny = v->ny;
@@ -257,6 +256,8 @@ void pack_trace(lp::TraceParams& T, const lf_volume* v, const lf_medium* e, cons
         T.gcell[a] = (float)(T.grid_n / ext);
         T.gcw[a] = (float)(ext / T.grid_n);
     }
+    T.glast = (float)(T.grid_n - 1);
+    T.gpitch = (float)(T.grid_n + 2);
     T.nz = v->nz;
     T.surface = p->surface;
     T.iso = p->iso;

@@ -82,7 +82,6 @@ struct TraceParams {
     int32_t dtype;
     unsigned long long* stats;
     int32_t part_log2;  // work items per ray = 2^part_log2 sample ranges
-    int32_t waves;      // forward kernels: waves per SIMD the registers are budgeted for (3 or 4)
     float* part_sums;   // forward with several ranges: [rows][N][ranges][3]
     // SF points of both sets (workspace tables filled by sf_point with
     // inv_n = 1/n in FP32, the values the kernel would compute)
@@ -115,6 +114,7 @@ struct TraceParams {
     int32_t vtx, vtiles;             // tiles per image row, tiles per view
     float gcell[3];                  // cells per world unit
     float gcw[3];                    // cell width
+    float glast, gpitch;             // grid_n - 1, grid_n + 2 (the padded grid's pitch)
     const float* maj;
     // adjoint: compacted list of rays with a nonzero adjoint and its length
     uint32_t* ray_list;
@@ -286,7 +286,7 @@ __device__ __forceinline__ TF classify(const PT& P, const float4* lut_e, const f
     const float s = __builtin_amdgcn_fmed3f((raw - P.vmin) * P.vscale, 0.0f, 1.0f);
     const float u = s * P.lut_last;
     t.l0 = min((int)u, P.lut_n - 2);
-    t.w = u - (float)t.l0;
+    t.w = fmaf(s, P.lut_last, -(float)t.l0);
     const float Aw = lut_e[t.l0].w, Bw = lut_e[t.l0 + 1].w;
     t.a = fmaf(t.w, Bw - Aw, Aw);
     if constexpr (MODE == kFrozen) {
@@ -315,27 +315,24 @@ __device__ __forceinline__ f3 rcp3(f3 d) { return mk3(rcp(d.x), rcp(d.y), rcp(d.
 // reciprocals of d's components (rcp3).
 __device__ __forceinline__ bool clip_box(f3 bmin, f3 bmax, f3 o, f3 d, f3 id, float& tn, float& tf) {
     float t0 = 0.0f, t1 = 3.402823466e38f;
+    bool in = true;
     const float oo[3] = {o.x, o.y, o.z}, dd[3] = {d.x, d.y, d.z}, ii[3] = {id.x, id.y, id.z};
     const float lo[3] = {bmin.x, bmin.y, bmin.z}, hi[3] = {bmax.x, bmax.y, bmax.z};
+    // formed with selects: lanes with a zero component cost the others no
+    // divergent branch per axis
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (dd[a] == 0.0f) {
-            if (oo[a] < lo[a] || oo[a] > hi[a]) return false;
-            continue;
-        }
-        const float inv = ii[a];
-        float ta = (lo[a] - oo[a]) * inv, tb = (hi[a] - oo[a]) * inv;
-        if (ta > tb) {
-            const float t = ta;
-            ta = tb;
-            tb = t;
-        }
-        t0 = fmaxf(t0, ta);
-        t1 = fminf(t1, tb);
+        const bool flat = dd[a] == 0.0f;  // no bounds on t along this axis, in or out
+        const float ta = (lo[a] - oo[a]) * ii[a], tb = (hi[a] - oo[a]) * ii[a];
+        const bool swap = ta > tb;
+        const float near = swap ? tb : ta, far = swap ? ta : tb;
+        t0 = flat ? t0 : fmaxf(t0, near);
+        t1 = flat ? t1 : fminf(t1, far);
+        in = in & !(flat & ((oo[a] < lo[a]) | (oo[a] > hi[a])));
     }
     tn = t0;
     tf = t1;
-    return t0 < t1;
+    return in & (t0 < t1);
 }
 
 __device__ __forceinline__ bool clip_box(f3 bmin, f3 bmax, f3 o, f3 d, float& tn, float& tf) {
@@ -380,7 +377,17 @@ __device__ __forceinline__ float hg_mu(float g, float u) {
     return fminf(fmaxf(mu, -1.0f), 1.0f);
 }
 
-__device__ __forceinline__ float neg_log1m(float u) { return -__logf(1.0f - u); }
+// -ln(1 - u) for u = k 2^-24 in [0, 1): 1 - u is exact and a normal number, so
+// the hardware base-2 logarithm needs no scaling of denormal arguments and no
+// test for infinities (seven instructions of the general logarithm).  ln 2 is
+// the sum of two floats (the first rounded towards zero), and the rounding
+// error of the first product is added back by a fused multiply-add.
+__device__ __forceinline__ float neg_log1m(float u) {
+    constexpr float kLn2Hi = 0.6931471228599548f, kLn2Lo = 5.769998878690785e-08f;
+    const float y = __builtin_amdgcn_logf(1.0f - u);
+    const float p = y * kLn2Hi;
+    return -fmaf(y, kLn2Hi, fmaf(y, kLn2Lo, fmaf(y, kLn2Hi, -p)));
+}
 
 // ---------------------------------------------------------------------------
 // Majorant-grid walk (3-D DDA over the grid_n^3 cells along x + t d).  The
@@ -392,37 +399,34 @@ __device__ __forceinline__ float neg_log1m(float u) { return -__logf(1.0f - u); 
 // ---------------------------------------------------------------------------
 struct GridWalk {
     float t, tx, ty, tz, dx, dy, dz;
-    int ci;          // cell index in the padded grid (one border cell per side)
-    int sx, sy, sz;  // signed index steps along x, y, z (by the sign of d)
+    int ci;          // LDS address of the cell in the padded grid (one border cell per side, 8 bytes a cell)
+    int sx, sy, sz;  // signed steps of it along x, y, z (by the sign of d)
 
-    // id: the reciprocals of d's components (rcp3)
+    // mg: LDS address of the padded grid; id: the reciprocals of d's components (rcp3)
     template <class PT>
-    __device__ __forceinline__ void init(const PT& P, f3 x, f3 d, f3 id, float t0) {
-        const int G = P.grid_n;
+    __device__ __forceinline__ void init(const PT& P, uint32_t mg, f3 x, f3 d, f3 id, float t0) {
         const f3 p = fma3(d, t0, x);
         const float pp[3] = {p.x, p.y, p.z}, dd[3] = {d.x, d.y, d.z}, xx[3] = {x.x, x.y, x.z};
         const float ii[3] = {id.x, id.y, id.z};
-        int c[3];
-        float tm[3], dl[3];
+        // cell coordinates stay floats (whole numbers below 16, exact): the
+        // clamp is one median-of-three and the cell index two fused
+        // multiply-adds, where integers took a conversion per use and
+        // quarter-rate multiplies.  Selects instead of a branch per axis.
+        float c[3], tm[3], dl[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            c[a] = min(max((int)floorf((pp[a] - P.bmin[a]) * P.gcell[a]), 0), G - 1);
-            if (fabsf(dd[a]) < 1e-20f) {
-                tm[a] = 3.402823466e38f;
-                dl[a] = 0.0f;
-            } else {
-                const float inv = ii[a];
-                const float plane = fmaf((float)(c[a] + (dd[a] > 0.0f ? 1 : 0)), P.gcw[a], P.bmin[a]);
-                tm[a] = (plane - xx[a]) * inv;
-                dl[a] = P.gcw[a] * fabsf(inv);
-            }
+            c[a] = __builtin_amdgcn_fmed3f(floorf((pp[a] - P.bmin[a]) * P.gcell[a]), 0.0f, P.glast);
+            const bool flat = fabsf(dd[a]) < 1e-20f;
+            const float plane = fmaf(c[a] + (dd[a] > 0.0f ? 1.0f : 0.0f), P.gcw[a], P.bmin[a]);
+            tm[a] = flat ? 3.402823466e38f : (plane - xx[a]) * ii[a];
+            dl[a] = flat ? 0.0f : P.gcw[a] * fabsf(ii[a]);
         }
         t = t0;
-        const int Gp = G + 2;
-        ci = ((c[2] + 1) * Gp + (c[1] + 1)) * Gp + (c[0] + 1);
-        sx = d.x > 0.0f ? 1 : -1;
+        const int Gp = 8 * (P.grid_n + 2), Gq = Gp * (P.grid_n + 2);
+        ci = 8 * (int)fmaf(fmaf(c[2], P.gpitch, c[1]), P.gpitch, c[0]) + ((int)mg + Gq + Gp + 8);
+        sx = d.x > 0.0f ? 8 : -8;
         sy = d.y > 0.0f ? Gp : -Gp;
-        sz = d.z > 0.0f ? Gp * Gp : -Gp * Gp;
+        sz = d.z > 0.0f ? Gq : -Gq;
         tx = tm[0];
         ty = tm[1];
         tz = tm[2];
@@ -443,47 +447,55 @@ struct GridWalk {
     // measured from A, with the same majorant and cell exit), so the points
     // are the same; only trips whose cell holds both points or holds A and is
     // then left are merged.  All outcomes are formed with selects, so lanes
-    // that take different ones run a trip's instructions once.  mg holds each
-    // padded cell's majorant s and the hardware reciprocal of s.  The face
-    // crossed first is the one whose boundary equals the minimum, and the
-    // cell index moves by that axis's signed stride.  The grid in LDS carries
-    // a border of cells that repeat the edge cells, so a step that rounding
-    // carries one cell past the grid reads the edge cell's majorant; the
-    // segment ends at the box, within rounding of the last face, so no walk
-    // goes two cells past it (the index is clamped to the padded grid all the
-    // same).  Every step raises the smallest boundary by one cell width along
-    // its axis, so the loop reaches tend within
-    // 3 (grid_n * segment length / cell width + 2) steps.
+    // that take different ones run a trip's instructions once, and what the
+    // code after the loop needs is left in lane values rather than in
+    // conditions, which a divergent loop merges into masks on every trip: a
+    // target lies in its last cell when the variate left over is negative
+    // (while A is sought and not found it never is: tau >= room), and A keeps
+    // the segment's end until it is found.
+    // The LDS grid at address mg holds each padded cell's majorant s and the
+    // hardware reciprocal of s; ci is the cell's LDS address, the read's own.
+    // The face crossed first is the one whose boundary
+    // equals the minimum, and the cell index moves by that axis's signed
+    // stride.  The grid in LDS carries a border of cells that repeat the edge
+    // cells, so a step that rounding carries one cell past the grid reads the
+    // edge cell's majorant; the segment ends at the box, within rounding of
+    // the last face, so no walk goes two cells past it (the index is clamped
+    // to the padded grid all the same).  Every step raises the smallest
+    // boundary by one cell width along its axis, so the loop reaches tend
+    // within 3 (grid_n * segment length / cell width + 2) steps.
     template <class PT>
-    __device__ __forceinline__ void next2(const PT& P, const float2* mg, bool wantA, float tauA,
+    __device__ __forceinline__ void next2(const PT& P, uint32_t mg, bool wantA, float tauA,
                                           float tauB, float tend, float& tA, float& sbA, float& tB, float& sbB,
-                                          uint32_t& steps) {
-        const int Gp = P.grid_n + 2, last = Gp * Gp * Gp - 1;
+                                          float& rbB, uint32_t& steps) {
+        // (no contraction: the variate left over is a rounded product, then a
+        // difference, whichever form of the trip computes it)
+#pragma clang fp contract(off)
+        typedef const __attribute__((address_space(3))) float2 LdsCell;
+        const int Gp = P.grid_n + 2;
+        const unsigned last = mg + 8u * (unsigned)(Gp * Gp * Gp - 1);
+        const int stx = sx, sty = sy, stz = sz;
         bool seekA = wantA;  // still looking for A (else for B)
         float tau = wantA ? tauA : tauB;
-        tA = t;
         tend = __builtin_canonicalizef(tend);
-        // B is found, if at all, in the last trip: its point and majorant are
-        // taken from that trip after the loop; A not found by the end of the
-        // segment lies at tend
-        float s, thb;
-        bool hitB;
+        tA = wantA ? tend : t;
+        float2 m;
+        float from, taub;
         for (;;) {
-            const float2 m = mg[ci];
-            s = m.x;
+            m.x = ((LdsCell*)(uintptr_t)(uint32_t)ci)->x;
+            m.y = ((LdsCell*)(uintptr_t)(uint32_t)ci)->y;
+            const float s = m.x;
             const float tmin = fminf(fminf(tx, ty), tz);
             const float te = __builtin_amdgcn_fmed3f(tmin, tend, -3.402823466e38f);  // min(tmin, tend)
             const float room = s * fmaxf(te - t, 0.0f);
-            const float th = fmaf(tau, m.y, t);        // the current target's point (s > 0 when it lies here)
+            const float th = fmaf(tau, m.y, t);        // A's point, if it lies here (then s > 0)
             const bool hitA = seekA && tau < room;     // A lies in this cell
-            // B from A in the same cell, or B as the current target
-            const float tb0 = hitA ? th : t;
-            const float taub = hitA ? tauB : tau;
-            const float roomb = hitA ? s * fmaxf(te - th, 0.0f) : room;
-            thb = hitA ? fmaf(taub, m.y, tb0) : th;
-            hitB = (hitA || !seekA) && taub < roomb;
-            const bool end = !hitB && te >= tend;        // the segment ends in this cell
-            const bool step = !hitB && !end;             // on into the next cell
+            // B from A in the same cell, or the current target from the cell's entry
+            from = hitA ? th : t;
+            taub = hitA ? tauB : tau;
+            const float roomb = s * fmaxf(te - from, 0.0f);
+            const bool hit = taub < roomb;             // B lies in this cell
+            const bool step = !hit && te < tend;       // on into the next cell
             tA = hitA ? th : tA;
             sbA = hitA ? s : sbA;
             t = te;
@@ -491,17 +503,15 @@ struct GridWalk {
             seekA = seekA && !hitA;
             steps += step ? 1u : 0u;
             const bool bx = tx == tmin, by = !bx && ty == tmin, bz = !bx && !by;
-            // (exactly one of bx, by, bz holds: a sum of selects, not an indexed pick)
-            const int st = (bx ? sx : 0) + (by ? sy : 0) + (bz ? sz : 0);
-            ci = (int)min((unsigned)(ci + st), (unsigned)last);  // (a wrapped index clamps to last)
+            ci = (int)min((unsigned)(ci + (bx ? stx : (by ? sty : stz))), last);  // (a wrapped index clamps to last)
             tx += bx ? dx : 0.0f;
             ty += by ? dy : 0.0f;
             tz += bz ? dz : 0.0f;
             if (!step) break;
         }
-        tA = seekA ? tend : tA;
-        tB = hitB ? thb : tend;
-        sbB = s;
+        tB = tau < 0.0f ? fmaf(taub, m.y, from) : tend;
+        sbB = m.x;
+        rbB = m.y;
     }
 };
 

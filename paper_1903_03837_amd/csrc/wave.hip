@@ -52,19 +52,23 @@ namespace lp {
 // the plain kernel spends no registers on them).  VIEWS: ground-truth views
 // (pinhole rays of pixel tiles) instead of light-field rays, also a separate
 // instantiation so that the light-field kernel carries none of its code.
-// WAVES: resident waves per SIMD the registers are budgeted for (3: up to 168
-// VGPRs; 4: 128, with a few values spilled).  The code and its results are
-// the same; four waves hide more latency where HBM has room to spare.
-template <int VT, int MODE, bool STATS, bool VIEWS, int WAVES>
-__global__ __launch_bounds__(256, WAVES) void gen_wave_kernel(TraceParams P) {
+// Registers are budgeted for four resident waves per SIMD (128 VGPRs; frozen
+// sampling and the adjoint spill a few values).  Other budgets measured: five
+// waves (96) take the 256^3 u16 step from 58 to 71 ms and views from 17.3 to
+// 20.6 ms; three resident waves take the 512^3 field at N = 32768 from 152 to
+// 167 ms per 2048 rows, and the adjoint of a dense 128^3 training pass from
+// 17.4 to 17.8 ms.
+template <int VT, int MODE, bool STATS, bool VIEWS>
+__global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
+    // LDS: cell majorants and their reciprocals (first, so that the grid walk's
+    // byte offsets are its addresses), then the tables
     extern __shared__ float4 smem[];
-    float4* lut_e = smem;
-    float4* lut_s = smem + (MODE == kFrozen ? P.lut_n : 0);
-    float* glds = (float*)(smem + P.lut_n);  // kGrad: dLUT [lut_n][4], dscale
-    // cell majorants and their reciprocals after the tables above (8-byte aligned)
-    float2* mg = (float2*)((float*)smem + ((4 * P.lut_n * (MODE == kFrozen ? 2 : 1) +
-                                            (MODE == kGrad ? 4 * P.lut_n + 1 : 0) + 1) & ~1));
     const int ncell = (P.grid_n + 2) * (P.grid_n + 2) * (P.grid_n + 2);  // padded grid
+    float2* mg = (float2*)smem;
+    const uint32_t mga = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float2*)mg;  // its LDS address
+    float4* lut_e = smem + (ncell + 1) / 2;
+    float4* lut_s = lut_e + (MODE == kFrozen ? P.lut_n : 0);
+    float* glds = (float*)(lut_e + P.lut_n);  // kGrad: dLUT [lut_n][4], dscale
     for (int e = threadIdx.x; e < P.lut_n; e += blockDim.x) {
         lut_e[e] = ((const float4*)P.lut_e)[e];
         if constexpr (MODE == kFrozen) lut_s[e] = ((const float4*)P.lut_s)[e];
@@ -418,73 +422,61 @@ __global__ __launch_bounds__(256, WAVES) void gen_wave_kernel(TraceParams P) {
             }
 
             // -------------------------------------------- two tentative points
-            bool ev_end = false, ev_real = false;
-            f3 ynew = x;
-            TF te;
-            te.l0 = 0;
-            te.w = 0.0f;
-            te.a = te.a_s = 0.0f;
             if (stepA || stepB) {
                 // (stepB always holds here; stepA is off for the first point of a sample)
-                const f3 sd = mode == kFlight ? dir : om;
+                const bool flight = mode == kFlight;
+                const f3 sd = flight ? dir : om;
                 GridWalk gw;
-                gw.init(P, x, sd, isd, t);
-                float sbA = 0.0f, sbB = 0.0f, tA, tB;
+                gw.init(P, mga, x, sd, isd, t);
+                float sbA = 0.0f, sbB = 0.0f, rbB = 0.0f, tA, tB;
                 // The walk is a chain of dependent steps (an LDS read of the
-                // cell's majorant, then ~40 instructions) that the wave's
+                // cell's majorant, then ~30 instructions) that the wave's
                 // slowest lane drags out; raised wave priority lets it issue
                 // ahead of the other waves of its SIMD, whose volume loads are
-                // in flight meanwhile.  With 3 waves per SIMD (the HBM-bound
-                // budget) the volume fetch that follows runs at that priority
-                // too; with 4 it must not (20 % slower).  Scheduling only:
-                // the same instructions and results.  Measured in the forward
-                // modes (N = 32768 at 3 waves 4524 -> 4465 -> 4370 ms, N = 8192
-                // at 4 waves 741 -> 729 ms); the adjoint keeps the default.
+                // in flight meanwhile (forward modes: 0.5-1 %; the adjoint
+                // keeps the default).  Scheduling only: the same instructions
+                // and results.
                 if constexpr (MODE != kGrad) __builtin_amdgcn_s_setprio(2);
-                gw.next2(P, mg, stepA, neg_log1m(u01(r.x)), neg_log1m(u01(r.z)), tend, tA, sbA, tB, sbB, cnt.cells);
+                gw.next2(P, mga, stepA, neg_log1m(u01(r.x)), neg_log1m(u01(r.z)), tend, tA, sbA, tB, sbB, rbB,
+                         cnt.cells);
                 if constexpr (MODE != kGrad) __builtin_amdgcn_s_setprio(0);
-                const f3 yA = fma3(sd, tA, x), yB = fma3(sd, tB, x);
-                if constexpr (MODE != kGrad && WAVES == 3) __builtin_amdgcn_s_setprio(2);
+                // (without a point A both fetches read point B's line)
+                const f3 yA = fma3(sd, stepA ? tA : tB, x), yB = fma3(sd, tB, x);
                 const float rawA = sample_volume<VT>(P, yA);
                 const float rawB = sample_volume<VT>(P, yB);
-                if constexpr (MODE != kGrad && WAVES == 3) __builtin_amdgcn_s_setprio(0);
-                bool more = true;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const bool use = h ? stepB : stepA;
-                    if (!use || !more) continue;
-                    const float th = h ? tB : tA;
-                    if (th >= tend) {
-                        ev_end = true;
-                        more = false;
-                        continue;
-                    }
-                    const TF tf = classify<MODE>(P, lut_e, lut_s, h ? rawB : rawA);
-                    const float sig_e = P.scale_e * tf.a;
-                    const float sb = h ? sbB : sbA;  // majorant of the point's cell
-                    t = th;
-                    if (mode == kFlight) {
-                        cnt.tent++;
-                        const float sig_s = MODE == kFrozen ? P.scale_s * tf.a_s : sig_e;
-                        if (u01(h ? r.w : r.y) * sb < sig_s) {
-                            ev_real = true;
-                            more = false;
-                            ynew = h ? yB : yA;
-                            te = tf;
-                            if constexpr (MODE == kFrozen) W *= sig_e / sig_s;
-                            if constexpr (MODE == kGrad)
-                                if (pass) G.sigma(tf, P.scale_e, dot(adj, ltot - L) / sig_e);
-                        } else {
-                            if constexpr (MODE == kFrozen) W *= (sb - sig_e) / (sb - sig_s);
-                            if constexpr (MODE == kGrad)
-                                if (pass) G.sigma(tf, P.scale_e, -dot(adj, ltot - L) / (sb - sig_e));
-                        }
-                    } else if (mode == kShadow) {
-                        cnt.shadow++;
-                        Tr *= 1.0f - sig_e * rcp(sb);
-                    } else {
-                        if constexpr (MODE == kGrad) G.sigma(tf, P.scale_e, -rc / (sb - sig_e));
-                    }
+                // Both points are classified and decided in straight-line code:
+                // lanes in flight, in shadow or with one point only differ by
+                // selects (nested branches ran every side in nearly every wave,
+                // with copies of the values that cross them).
+                const TF fA = classify<MODE>(P, lut_e, lut_s, rawA), fB = classify<MODE>(P, lut_e, lut_s, rawB);
+                const float sgA = P.scale_e * fA.a, sgB = P.scale_e * fB.a;
+                const float ssA = MODE == kFrozen ? P.scale_s * fA.a_s : sgA;
+                const float ssB = MODE == kFrozen ? P.scale_s * fB.a_s : sgB;
+                const bool inA = stepA && !(tA >= tend);                       // A lies on the segment
+                const bool realA = inA && flight && u01(r.y) * sbA < ssA;      // and is a real collision
+                const bool reachB = !stepA || (inA && !realA);                 // B is looked at
+                const bool inB = reachB && !(tB >= tend);
+                const bool realB = inB && flight && u01(r.w) * sbB < ssB;
+                const bool ev_end = (stepA && !inA) || (reachB && !inB), ev_real = realA || realB;
+                t = inB ? tB : (inA ? tA : t);
+                if (flight) cnt.tent += (inA ? 1u : 0u) + (inB ? 1u : 0u);
+                if (mode == kShadow) cnt.shadow += (inA ? 1u : 0u) + (inB ? 1u : 0u);
+                // ratio tracking (Tr is set anew for each shadow ray, so lanes in
+                // flight may spoil it; the replay of a shadow ray may not)
+                const bool ratio = MODE != kGrad || mode == kShadow;
+                Tr *= inA && ratio ? fmaf(-rcp(sbA), sgA, 1.0f) : 1.0f;
+                Tr *= inB && ratio ? fmaf(-rbB, sgB, 1.0f) : 1.0f;
+                if constexpr (MODE == kFrozen) {
+                    if (inA && flight) W *= realA ? sgA / ssA : (sbA - sgA) / (sbA - ssA);
+                    if (inB && flight) W *= realB ? sgB / ssB : (sbB - sgB) / (sbB - ssB);
+                }
+                if constexpr (MODE == kGrad) {
+                    // scores: d sigma / sigma at a real collision, -d sigma /
+                    // (sigma_bar - sigma) at a null one and at a shadow step
+                    const bool on = flight ? pass != 0 : mode == kShadow2;
+                    const float gain = flight ? dot(adj, ltot - L) : rc;
+                    if (on && inA) G.sigma(fA, P.scale_e, (realA ? gain : -gain) / (realA ? sgA : sbA - sgA));
+                    if (on && inB) G.sigma(fB, P.scale_e, (realB ? gain : -gain) / (realB ? sgB : sbB - sgB));
                 }
                 if (ev_end) {
                     if (mode == kFlight) {
@@ -507,6 +499,9 @@ __global__ __launch_bounds__(256, WAVES) void gen_wave_kernel(TraceParams P) {
                     }
                 } else if (ev_real) {
                     cnt.real++;
+                    TF te;
+                    te.l0 = realB ? fB.l0 : fA.l0;
+                    te.w = realB ? fB.w : fA.w;
                     const f3 rgb = tf_rgb(lut_e, te);
                     if constexpr (MODE == kGrad) {
                         if (pass) {
@@ -523,7 +518,7 @@ __global__ __launch_bounds__(256, WAVES) void gen_wave_kernel(TraceParams P) {
                                 }
                         }
                     }
-                    x = ynew;
+                    x = realB ? yB : yA;
                     T = T * mk3(__builtin_amdgcn_fmed3f(rgb.x, 0.0f, 1.0f), __builtin_amdgcn_fmed3f(rgb.y, 0.0f, 1.0f),
                                 __builtin_amdgcn_fmed3f(rgb.z, 0.0f, 1.0f));
                     if (T.x == 0.0f && T.y == 0.0f && T.z == 0.0f) {
@@ -703,21 +698,21 @@ hipError_t launch_active_rays(const TraceParams& P, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int VT, int MODE, bool STATS, bool VIEWS, int WAVES>
-static hipError_t launch_wave_w(const TraceParams& P, hipStream_t s) {
+template <int VT, int MODE, bool STATS, bool VIEWS>
+static hipError_t launch_wave_t(const TraceParams& P, hipStream_t s) {
     const long long rows = P.row_end - P.row_begin;
     const long long ntiles = (P.views ? (long long)P.nviews * P.vtiles : ((rows + 7) / 8) * (long long)((P.N + 7) / 8))
                              << P.part_log2;
     if (ntiles <= 0) return hipSuccess;
     const size_t ncell = (size_t)(P.grid_n + 2) * (P.grid_n + 2) * (P.grid_n + 2);  // padded grid in LDS
     const size_t lds = sizeof(float4) * (size_t)P.lut_n * (MODE == kFrozen ? 2 : 1) +
-                       (MODE == kGrad ? sizeof(float) * (4 * (size_t)P.lut_n + 1) : 0) + sizeof(float) +
-                       sizeof(float2) * ncell;
+                       (MODE == kGrad ? sizeof(float) * (4 * (size_t)P.lut_n + 1) : 0) +
+                       sizeof(float4) * ((ncell + 1) / 2);
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gen_wave_kernel<VT, MODE, STATS, VIEWS, WAVES>, 256,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gen_wave_kernel<VT, MODE, STATS, VIEWS>, 256,
                                                          lds);
     if (e != hipSuccess) return e;
     long long blocks = (long long)cus * (per_cu > 0 ? per_cu : 1);
@@ -725,17 +720,8 @@ static hipError_t launch_wave_w(const TraceParams& P, hipStream_t s) {
     // waves that find no chunk exit at once)
     const long long need = (ntiles + 3) / 4;
     if (blocks > need) blocks = need;
-    gen_wave_kernel<VT, MODE, STATS, VIEWS, WAVES><<<(unsigned)blocks, 256, lds, s>>>(P);
+    gen_wave_kernel<VT, MODE, STATS, VIEWS><<<(unsigned)blocks, 256, lds, s>>>(P);
     return hipGetLastError();
-}
-
-// The adjoint is budgeted for three waves (at four it spills ~32 values and
-// runs slower); the forward modes take P.waves.
-template <int VT, int MODE, bool STATS, bool VIEWS>
-static hipError_t launch_wave_t(const TraceParams& P, hipStream_t s) {
-    if constexpr (MODE != kGrad)
-        if (P.waves == 4) return launch_wave_w<VT, MODE, STATS, VIEWS, 4>(P, s);
-    return launch_wave_w<VT, MODE, STATS, VIEWS, 3>(P, s);
 }
 
 template <int VT>
