@@ -43,7 +43,8 @@ size_t brick_copy_bytes(const lf_volume* v) {
     return align256(esz * brick_voxels(v));
 }
 
-// lf_generate workspace: majorant (offset 0), 8 tile counters (offset 64),
+// lf_generate workspace: majorant (offset 0), 8 tile counters (offset 64; in
+// the queue's buffer where many waves contend for them),
 // spatial order of the generated origin rows (offset 256), spatial order of
 // the directions, the cell majorants of the grid (when used), the point
 // tables of both SF sets, then the brick copy of the volume.
@@ -80,12 +81,56 @@ int view_part_log2(int spp, unsigned long long pixels) {
     return by_spp < by_px ? by_spp : by_px;
 }
 
-size_t part_sums_bytes(const lf_gen_params* p) {
-    if (p->surface) return 0;
-    const int pl = part_log2(p, true);
-    if (pl == 0) return 0;
+// The work queue's buffer: tile counters a cache line apart, then the samples
+// of the finely split rays, then the ranges' sums.
+constexpr int kCtrStride = 32;                           // counters, in uint32
+constexpr size_t kCtrBytes = 4 * kCtrStride * lp::kParts;
+
+// Work items of a forward whose mean sums 2^log2 ranges of a ray's samples.  A
+// lane walks its item's samples one after the other, so when the queue runs
+// dry most lanes still hold part of an item, and the longest sets the time:
+// with 32-sample items (256^3, N = 2048, 64 spp) the last 12 of 71 ms went by
+// after the queue was dry.  So the last rays of the queue are split down to
+// two samples per item (one where the launch is small), their samples kept
+// and summed by a second kernel in the same order (same bits).  They make up
+// four ordinary items of every lane of the full grid (2^18 lanes), enough to
+// fill the gaps that the longest ordinary items leave, and at most 2^25
+// samples (403 MB).  Below 8 samples per ray there is little to split.
+// Measured: 256^3 step 58.0 -> 53.0 ms (two items per lane instead of four
+// 55.5, eight 53.4; one or four samples per item 53.5), views at 256 spp 17.1
+// -> 15.5 ms, 128^3 training pass 18.7 -> 18.1 ms; 64^3, N = 256, 16 spp 1.18
+// -> 0.50 ms with the counters below (two samples per item 0.63).
+struct Items {
+    int log2 = 0;                       // ranges per ray
+    int fine_units = 0, fine_log2 = 0;  // ray tiles of each part split finely, their items per ray
+    // the buffer: padded counters (when used), kept samples, range sums
+    size_t ctr = 0, samples = 0, sums = 0;
+    size_t bytes() const { return ctr + samples + sums; }
+};
+Items work_items(unsigned long long rays, long long ray_tiles, int spp, int log2) {
+    Items it;
+    it.log2 = it.fine_log2 = log2;
+    if (log2) it.sums = align256((size_t)(12 * rays) << log2);
+    if (spp >= 8) {
+        const long long by_lanes = (1ll << 20) >> log2, by_memory = (1ll << 25) / spp;
+        const long long part = (ray_tiles + lp::kParts - 1) / lp::kParts;
+        const long long fine = (std::min(by_lanes, by_memory) / 64 + lp::kParts - 1) / lp::kParts;
+        it.fine_units = (int)std::min(part, fine);
+        // two samples per item, or one where even that leaves a lane few items
+        const int least = rays * (unsigned long long)spp < (1ull << 22) ? 1 : 2;
+        while ((spp >> it.fine_log2) > least) ++it.fine_log2;
+        it.samples = align256(12 * (size_t)(64ll * it.fine_units * lp::kParts) * (size_t)spp);
+        if (it.fine_units == part) it.sums = 0;  // every ray's samples are kept
+    }
+    if (it.fine_units || ray_tiles > 4096) it.ctr = kCtrBytes;
+    return it;
+}
+Items field_items(const lf_gen_params* p) {
+    if (p->surface) return {};
     const long long re = p->row_end <= 0 ? stored_rows(p) : p->row_end;
-    return align256(12 * (size_t)(re - p->row_begin) * (size_t)p->N << pl);
+    const long long rows = re - p->row_begin;
+    return work_items((unsigned long long)rows * (unsigned long long)p->N, (rows + 7) / 8 * ((p->N + 7) / 8), p->spp,
+                      part_log2(p, true));
 }
 
 // Cells per axis of the majorant grid in use (0: the global majorant).
@@ -266,6 +311,19 @@ void pack_trace(lp::TraceParams& T, const lf_volume* v, const lf_medium* e, cons
     T.half_voxel = (float)(0.5 * hv);
 }
 
+// Points T at the buffer's parts (before set-up, which clears the counters).
+void set_items(lp::TraceParams& T, const Items& items, char* buffer) {
+    T.part_log2 = items.log2;
+    T.fine_units = items.fine_units;
+    T.fine_log2 = items.fine_log2;
+    if (items.ctr) {
+        T.tile_ctr = (unsigned int*)buffer;
+        T.ctr_stride = kCtrStride;
+    }
+    T.samples = (float*)(buffer + items.ctr);
+    T.part_sums = (float*)(buffer + items.ctr + items.samples);
+}
+
 // Isosurface variant: cells of the raw-range grid (the majorant grid size,
 // 8 when none is set) and their bytes in the workspace.
 int surface_cells(const lf_gen_params* p) { return p->majorant_grid > 0 ? p->majorant_grid : 8; }
@@ -279,11 +337,13 @@ size_t surface_range_bytes(const lf_gen_params* p) {
 hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium* m, const lf_gen_params* p,
                        char* w, float* range, hipStream_t s) {
     float* sig = (float*)w;
-    unsigned int* ctr = (unsigned int*)(w + 64);
     int32_t* perm_o = (int32_t*)(w + 256);
     int32_t* perm_d = (int32_t*)(w + 256 + align256(4 * (size_t)(T.row_end - T.row_begin)));
     T.sigbar = sig;
-    T.tile_ctr = ctr;
+    if (!T.tile_ctr) {  // no counters a cache line apart (set_items)
+        T.tile_ctr = (unsigned int*)(w + 64);
+        T.ctr_stride = 1;
+    }
     T.perm_o = perm_o;
     T.perm_d = perm_d;
     const int G = surface_cells(p);
@@ -294,7 +354,7 @@ hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium
         T.gcw[a] = (float)(ext / G);
     }
     T.srange = range;
-    hipError_t e = lp::launch_wave_setup(T, m->lut, m->lut_size, m->density_scale, p->majorant, sig, ctr, perm_o,
+    hipError_t e = lp::launch_wave_setup(T, m->lut, m->lut_size, m->density_scale, p->majorant, sig, perm_o,
                                          perm_d, s);
     if (e == hipSuccess)
         e = lp::launch_majorant_grid(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, G, m->lut,
@@ -309,11 +369,13 @@ hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium
 hipError_t setup_tracking(lp::TraceParams& T, const lf_volume* vol, const lf_medium* sm, const lf_gen_params* p,
                           char* w, hipStream_t s) {
     float* sig = (float*)w;
-    unsigned int* ctr = (unsigned int*)(w + 64);
     int32_t* perm_o = (int32_t*)(w + 256);
     int32_t* perm_d = (int32_t*)(w + 256 + align256(4 * (size_t)(T.row_end - T.row_begin)));
     T.sigbar = sig;
-    T.tile_ctr = ctr;
+    if (!T.tile_ctr) {  // no counters a cache line apart (set_items)
+        T.tile_ctr = (unsigned int*)(w + 64);
+        T.ctr_stride = 1;
+    }
     T.perm_o = perm_o;
     T.perm_d = perm_d;
     T.maj = sig;
@@ -321,8 +383,8 @@ hipError_t setup_tracking(lp::TraceParams& T, const lf_volume* vol, const lf_med
     float4* tab_d = (float4*)((char*)tab_o + align256(16 * (size_t)p->M));
     T.tab_o = tab_o;
     T.tab_d = tab_d;
-    hipError_t e = lp::launch_wave_setup(T, sm->lut, sm->lut_size, sm->density_scale, p->majorant, sig, ctr,
-                                         perm_o, perm_d, s);
+    hipError_t e = lp::launch_wave_setup(T, sm->lut, sm->lut_size, sm->density_scale, p->majorant, sig, perm_o,
+                                         perm_d, s);
     if (e == hipSuccess) e = lp::launch_sf_table(p->M, 1.0f / (float)p->M, tab_o, s);
     if (e == hipSuccess) e = lp::launch_sf_table(p->N, 1.0f / (float)p->N, tab_d, s);
     if (e == hipSuccess && grid_cells(p) > 0) {
@@ -383,8 +445,9 @@ int lf_generate(const lf_volume* vol, const lf_medium* eval, const lf_medium* sa
     if (!lf_out) return fail(LF_E_ARG, "lf_out is NULL");
     if (params->surface && sample && sample != eval)
         return fail(LF_E_UNSUPPORTED, "frozen sampling does not apply to the isosurface variant");
+    const Items items = field_items(params);
     const size_t need =
-        gen_order_bytes(params) + brick_copy_bytes(vol) + surface_range_bytes(params) + part_sums_bytes(params);
+        gen_order_bytes(params) + brick_copy_bytes(vol) + surface_range_bytes(params) + items.bytes();
     r = check_workspace(ws, ws_bytes, need);
     if (r == 1) {
         *ws_bytes = need;
@@ -406,13 +469,12 @@ int lf_generate(const lf_volume* vol, const lf_medium* eval, const lf_medium* sa
         if (e != hipSuccess) return hip_fail(e, "lf_generate (isosurface)");
         return LF_OK;
     }
+    set_items(T, items, w + gen_order_bytes(params) + brick_copy_bytes(vol) + surface_range_bytes(params));
     if (e == hipSuccess) e = setup_tracking(T, vol, sm, params, w, s);
     if (e != hipSuccess) return hip_fail(e, "lf_generate (set-up)");
     const int mode = (sample && sample != eval) ? lp::kFrozen : lp::kFwd;
-    T.part_log2 = part_log2(params, true);
-    T.part_sums = (float*)(w + gen_order_bytes(params) + brick_copy_bytes(vol) + surface_range_bytes(params));
     e = lp::launch_generate_wave(T, vol->type, mode, s);
-    if (e == hipSuccess && T.part_log2 > 0) e = lp::launch_combine_parts(T, s);
+    if (e == hipSuccess) e = lp::launch_combine_parts(T, s);
     if (e != hipSuccess) return hip_fail(e, "lf_generate");
     return LF_OK;
 }
@@ -481,9 +543,10 @@ int lf_render_views(const lf_volume* vol, const lf_medium* medium, const lf_ligh
     const size_t views_bytes = align256(sizeof(lp::ViewCam) * (size_t)n_views);
     const unsigned long long pixels = (unsigned long long)n_views * (unsigned long long)W * (unsigned long long)H;
     const int vpl = p1.surface ? 0 : view_part_log2(p1.spp, pixels);
-    const size_t psum_bytes = vpl ? align256((size_t)(12 * pixels) << vpl) : 0;
+    const long long view_tiles = (long long)n_views * ((W + 7) / 8) * ((H + 7) / 8);
+    const Items items = p1.surface ? Items{} : work_items(pixels, view_tiles, p1.spp, vpl);
     const size_t need =
-        gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1) + psum_bytes;
+        gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1) + items.bytes();
     r = check_workspace(ws, ws_bytes, need);
     if (r == 1) {
         *ws_bytes = need;
@@ -521,11 +584,10 @@ int lf_render_views(const lf_volume* vol, const lf_medium* medium, const lf_ligh
             e = run_surface(T, vol, medium, &p1, w,
                             (float*)(w + gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol)), s);
     } else {
+        set_items(T, items, w + gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1));
         if (e == hipSuccess) e = setup_tracking(T, vol, medium, &p1, w, s);
-        T.part_log2 = vpl;
-        T.part_sums = (float*)(w + gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1));
         if (e == hipSuccess) e = lp::launch_generate_wave(T, vol->type, lp::kFwd, s);
-        if (e == hipSuccess && vpl > 0) e = lp::launch_combine_parts(T, s);
+        if (e == hipSuccess) e = lp::launch_combine_parts(T, s);
     }
     if (e != hipSuccess) return hip_fail(e, "lf_render_views");
     return LF_OK;
@@ -631,7 +693,7 @@ int lf_generate_backward(const lf_volume* vol, const lf_medium* medium, const lf
     // then the brick copy of the volume
     const long long re = params->row_end <= 0 ? stored_rows(params) : params->row_end;
     const size_t list_bytes = align256(4 * (size_t)(re - params->row_begin) * (size_t)params->N);
-    const size_t need = gen_order_bytes(params) + list_bytes + brick_copy_bytes(vol);
+    const size_t need = gen_order_bytes(params) + list_bytes + brick_copy_bytes(vol) + kCtrBytes;
     r = check_workspace(ws, ws_bytes, need);
     if (r == 1) {
         *ws_bytes = need;
@@ -649,6 +711,8 @@ int lf_generate_backward(const lf_volume* vol, const lf_medium* medium, const lf
     T.ray_count = (unsigned int*)(w + 64) + 8;
     T.ray_list = (uint32_t*)(w + gen_order_bytes(params));
     T.vol = w + gen_order_bytes(params) + list_bytes;
+    T.tile_ctr = (unsigned int*)(w + gen_order_bytes(params) + list_bytes + brick_copy_bytes(vol));
+    T.ctr_stride = kCtrStride;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = lp::launch_halo_bricks(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, (void*)T.vol, s);
     if (e == hipSuccess) e = lp::launch_zero(d_lut, 4ll * medium->lut_size, s);

@@ -76,8 +76,7 @@ inline int halo_bricks(int n) { return (n - 2) / 3 + 1; }
 hipError_t launch_halo_bricks(const void* src, int vtype, int layout, int nx, int ny, int nz, void* dst,
                               hipStream_t s);
 hipError_t launch_wave_setup(const TraceParams& P, const float* sample_lut, int lut_n, float sample_scale,
-                             float given, float* sigbar, unsigned int* ctr, int32_t* perm_o, int32_t* perm_d,
-                             hipStream_t s);
+                             float given, float* sigbar, int32_t* perm_o, int32_t* perm_d, hipStream_t s);
 hipError_t launch_majorant_grid(const void* vol, int vtype, int layout, int nx, int ny, int nz, int G,
                                 const float* lut, int lut_n, float scale, double vmin, double vmax, float* out,
                                 float* range, hipStream_t s);

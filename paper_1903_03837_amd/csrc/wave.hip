@@ -92,25 +92,29 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
     // grid long after most waves are done).  Adjoint: the scores add up in
     // any order.  Forward with more than one range: each item leaves its
     // partial sum in part_sums, and a second kernel adds the ranges in order.
+    // The last rays of each part of the queue are split further, down to a
+    // sample or two per item: their samples are kept, and summed by a second
+    // kernel in the same order.
     const long long nlist = MODE == kGrad ? (long long)*P.ray_count << P.part_log2 : 0;
-    const long long ntiles = MODE == kGrad ? (nlist + 63) / 64
-                             : VIEWS     ? ((long long)P.nviews * P.vtiles) << P.part_log2
-                                         : ((long long)((P.row_end - P.row_begin + 7) / 8) * ((P.N + 7) / 8))
-                                               << P.part_log2;
+    const Queue Q(MODE == kGrad ? (nlist + 63) / 64
+                  : VIEWS       ? (long long)P.nviews * P.vtiles
+                                : (long long)((P.row_end - P.row_begin + 7) / 8) * ((P.N + 7) / 8),
+                  MODE == kGrad ? 0 : P.part_log2, MODE == kGrad ? 0 : P.fine_units, P.fine_log2);
     const int home = blockIdx.x % kParts;
+    const int place = (int)(blockIdx.x / kParts) * 4 + (int)(threadIdx.x >> 6);  // among the part's waves
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
-    // wave-uniform queue cursor: rays [cur, end) of the current tile
-    long long cur = 0, end = 0;
+    // wave-uniform queue cursor
+    Tile tile = {0, 0, 0, 0, false};
     unsigned dry = 0;
-    bool drained = false;
+    bool begun = false, drained = false;
 
     // lane state
     int mode = kIdle;
     uint32_t k = 0, blk = 0;
     int s = 0, b = 0;
     int s_end = P.spp;  // end of this work item's sample range
-    int part = 0;       // its range index
+    int part = 0;       // its range index, or (fine items) the ray in the samples buffer with the top bit set
     f3 po = mk3(0, 0, 0), d0 = po, acc = po, x = po, dir = po, T = po, L = po, om = po, C = po;
     float W = 1.0f, t = 0.0f, tend = 0.0f, Tr = 1.0f, up0 = 0.0f, up1 = 0.0f;
     f3 isd = po;  // reciprocals of the current segment's direction (dir or om)
@@ -161,10 +165,17 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     o[1] = L.y;
                     o[2] = L.z;
                 }
+                if (part < 0) {
+                    float* o = P.samples + 3 * ((uint64_t)(part & 0x7fffffff) * (uint32_t)P.spp + (uint32_t)s);
+                    o[0] = L.x;
+                    o[1] = L.y;
+                    o[2] = L.z;
+                }
             }
             if (next && ++s == s_end) {
                 if constexpr (MODE != kGrad) {
-                    if (parts == 1) {
+                    if (part < 0) {  // fine item: its samples are summed later
+                    } else if (parts == 1) {
                         const float fs = (float)P.spp;
                         store_texel(P.out, P.dtype, k, mk3(acc.x / fs, acc.y / fs, acc.z / fs));
                     } else {  // this range's sum, for the combining kernel
@@ -188,37 +199,46 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
         if (idle) {
             const int nidle = __popcll(idle);
             const int rank = __popcll(idle & lt_mask);
-            long long avail = end - cur;
-            long long fresh = -1;
+            const long long avail = tile.end - tile.cur;
+            Tile fresh;
+            bool more = false;
             if (nidle > avail && !drained) {
-                long long tl = 0;
-                if (lane == 0) tl = next_tile(P.tile_ctr, ntiles, home, dry);
-                tl = __shfl(tl, 0, 64);
-                dry = __shfl(dry, 0, 64);
-                if (tl < 0) drained = true;
-                else fresh = tl * 64;
+                more = next_tile(P.tile_ctr, P.ctr_stride, Q, home, place, begun, dry, fresh);
+                drained = !more;
             }
             long long q = -1;
+            bool fine = tile.fine;
+            int lg = MODE == kGrad ? plog : tile.log2;
+            long long shift = tile.shift;
             if (mode == kIdle) {
-                if (rank < avail) q = cur + rank;
-                else if (fresh >= 0) q = fresh + (rank - avail);
+                if (rank < avail) {
+                    q = tile.cur + rank;
+                } else if (more) {
+                    q = fresh.cur + (rank - avail);
+                    if constexpr (MODE != kGrad) {
+                        fine = fresh.fine;
+                        lg = fresh.log2;
+                        shift = fresh.shift;
+                    }
+                }
             }
-            if (fresh >= 0) {
-                cur = fresh + (nidle - avail);
-                end = fresh + 64;
+            if (more) {
+                tile = fresh;
+                tile.cur += nidle - avail;
             } else {
-                cur += min((long long)nidle, avail);
+                tile.cur += min((long long)nidle, avail);
             }
             if (q >= 0) {
                 int i = -1, j = -1;
-                // work item q: sample range q mod parts of ray slot q / parts
-                int s_first = 0;
+                // work item q: sample range q mod 2^lg of ray slot q >> lg
+                const long long slot = q >> lg;
+                const int item = (int)q & ((1 << lg) - 1);
+                const int s_first = (item * P.spp) >> lg;
+                s_end = ((item + 1) * P.spp) >> lg;
+                part = fine ? (int)(0x80000000u | (uint32_t)(slot + shift)) : item;
                 if constexpr (MODE == kGrad) {
                     if (q < nlist) {
-                        part = (int)(q & (parts - 1));
-                        s_first = (part * P.spp) >> plog;
-                        s_end = ((part + 1) * P.spp) >> plog;
-                        const uint32_t kk = P.ray_list[q >> plog];
+                        const uint32_t kk = P.ray_list[slot];
                         i = (int)(kk / (uint32_t)P.N);
                         j = (int)(kk - (uint32_t)i * (uint32_t)P.N);
                         const float* a = P.d_lf + 3 * (uint64_t)kk;
@@ -227,10 +247,6 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     }
                 } else if constexpr (VIEWS) {
                     // pixel of an 8 x 8 tile of a view: the ray from the eye through its centre
-                    const long long slot = q >> plog;
-                    part = (int)(q & (parts - 1));
-                    s_first = (part * P.spp) >> plog;
-                    s_end = ((part + 1) * P.spp) >> plog;
                     const uint32_t t = (uint32_t)(slot >> 6);
                     const uint32_t v = t / (uint32_t)P.vtiles, rem = t - v * (uint32_t)P.vtiles;
                     const uint32_t ty = rem / (uint32_t)P.vtx, tx = rem - ty * (uint32_t)P.vtx;
@@ -251,10 +267,6 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                         mode = kStart;
                     }
                 } else {
-                    const long long slot = q >> plog;
-                    part = (int)(q & (parts - 1));
-                    s_first = (part * P.spp) >> plog;
-                    s_end = ((part + 1) * P.spp) >> plog;
                     int ti, tj;
                     tile_coords(slot >> 6, tiles_i, tiles_j, ti, tj);
                     const int oi = ti * 8 + (int)((slot >> 3) & 7), dj = tj * 8 + (int)(slot & 7);
@@ -267,9 +279,10 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     k = (uint32_t)i * (uint32_t)P.N + (uint32_t)j;
                     if (P.M == P.N && i == j) {
                         // no direction: texel 0 (never listed for the adjoint;
-                        // with several ranges the combining kernel writes it)
+                        // with several ranges or kept samples the summing kernel
+                        // writes it)
                         if constexpr (MODE != kGrad)
-                            if (parts == 1) store_texel(P.out, P.dtype, k, mk3(0.0f, 0.0f, 0.0f));
+                            if (parts == 1 && !fine) store_texel(P.out, P.dtype, k, mk3(0.0f, 0.0f, 0.0f));
                     } else {
                         const float4 a = P.tab_o[i], c = P.tab_d[j];
                         po = mk3(a.x, a.y, a.z);
@@ -285,8 +298,25 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                         // usual.  (The adjoint's ray list leaves such rays out.)
                         if constexpr (MODE != kGrad) {
                             if (misses_box(P, O, bmin, bmax, po, d0)) {
-                                if (!env_zero)
+                                if (fine) {  // all of the item's samples
+                                    float* o = P.samples + 3 * ((uint64_t)(part & 0x7fffffff) * (uint32_t)P.spp);
+                                    for (int s2 = s_first; s2 < s_end; ++s2) {
+                                        o[3 * s2 + 0] = env.x;
+                                        o[3 * s2 + 1] = env.y;
+                                        o[3 * s2 + 2] = env.z;
+                                    }
+                                    // (of the kept sample radiance, the last one of each range)
+                                    if (P.srad && ((item + 1) & ((1 << (lg - plog)) - 1)) == 0) {
+                                        float* r = P.srad + 3 * ((uint64_t)k * (uint32_t)P.spp + (uint32_t)(s_end - 1));
+                                        r[0] = env.x;
+                                        r[1] = env.y;
+                                        r[2] = env.z;
+                                    }
+                                    cnt.samples++;
+                                    mode = kIdle;
+                                } else if (!env_zero) {
                                     for (int s2 = s_first + 1; s2 < s_end; ++s2) acc = acc + env;
+                                }
                                 cnt.samples += (uint32_t)(s_end - 1 - s_first);
                                 s = s_end - 1;
                             }
@@ -295,8 +325,9 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                 }
             }
         }
-        if (__ballot(mode != kIdle) == 0) {
-            if (drained && end <= cur) break;
+        const int live = __popcll(__ballot(mode != kIdle));
+        if (live == 0) {
+            if (drained && tile.end <= tile.cur) break;
             continue;
         }
 
@@ -551,7 +582,7 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
             }
 
             if (sample_done) mode = kDone;
-            if (__popcll(__ballot(mode == kFlight || mode == kShadow || mode == kShadow2)) < kTrackPass) break;
+            if (__popcll(__ballot(mode == kFlight || mode == kShadow || mode == kShadow2)) * 64 < kTrackPass * live) break;
         }
     }
 
@@ -657,12 +688,13 @@ __global__ __launch_bounds__(256) void active_rays_kernel(TraceParams P) {
 }
 
 __global__ void wave_setup_kernel(const float* lut, int n, float scale, float given, float* sigbar,
-                                  unsigned int* ctr) {
+                                  unsigned int* ctr, int ctr_stride, unsigned int* ray_count) {
     __shared__ float red[256];
     float m = 0.0f;
     for (int e = threadIdx.x; e < n; e += 256) m = fmaxf(m, lut[4 * e + 3]);
     red[threadIdx.x] = m;
-    if (threadIdx.x < kParts + 1) ctr[threadIdx.x] = 0u;  // tile counters, then the list length
+    if (threadIdx.x < kParts) ctr[threadIdx.x * ctr_stride] = 0u;
+    if (threadIdx.x == kParts && ray_count) *ray_count = 0u;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
@@ -678,9 +710,9 @@ static int band_size(int n) {
 }
 
 hipError_t launch_wave_setup(const TraceParams& P, const float* sample_lut, int lut_n, float sample_scale,
-                             float given, float* sigbar, unsigned int* ctr, int32_t* perm_o, int32_t* perm_d,
-                             hipStream_t s) {
-    wave_setup_kernel<<<1, 256, 0, s>>>(sample_lut, lut_n, sample_scale, given, sigbar, ctr);
+                             float given, float* sigbar, int32_t* perm_o, int32_t* perm_d, hipStream_t s) {
+    wave_setup_kernel<<<1, 256, 0, s>>>(sample_lut, lut_n, sample_scale, given, sigbar, P.tile_ctr, P.ctr_stride,
+                                        P.ray_count);
     const int rows = P.row_end - P.row_begin;
     const int bo = band_size(P.M), bd = band_size(P.N);
     if (rows > 0) sf_order_kernel<<<(rows + bo - 1) / bo, 256, 0, s>>>(P.row_begin, rows, bo, perm_o);
@@ -698,11 +730,21 @@ hipError_t launch_active_rays(const TraceParams& P, hipStream_t s) {
     return hipGetLastError();
 }
 
+static long long ray_tiles(const TraceParams& P) {
+    return P.views ? (long long)P.nviews * P.vtiles
+                   : (long long)((P.row_end - P.row_begin + 7) / 8) * ((P.N + 7) / 8);
+}
+
 template <int VT, int MODE, bool STATS, bool VIEWS>
 static hipError_t launch_wave_t(const TraceParams& P, hipStream_t s) {
-    const long long rows = P.row_end - P.row_begin;
-    const long long ntiles = (P.views ? (long long)P.nviews * P.vtiles : ((rows + 7) / 8) * (long long)((P.N + 7) / 8))
-                             << P.part_log2;
+    // (adjoint: the list's length is only known on the device)
+    long long ntiles = 0;
+    if (MODE == kGrad) {
+        ntiles = ray_tiles(P) << P.part_log2;
+    } else {
+        const Queue Q(ray_tiles(P), P.part_log2, P.fine_units, P.fine_log2);
+        for (int p = 0; p < kParts; ++p) ntiles += Q.tiles(p);
+    }
     if (ntiles <= 0) return hipSuccess;
     const size_t ncell = (size_t)(P.grid_n + 2) * (P.grid_n + 2) * (P.grid_n + 2);  // padded grid in LDS
     const size_t lds = sizeof(float4) * (size_t)P.lut_n * (MODE == kFrozen ? 2 : 1) +
@@ -759,10 +801,57 @@ __global__ void combine_parts_kernel(TraceParams P, long long n) {
     store_texel(P.out, P.dtype, k, acc);
 }
 
+// Texels of the rays whose samples were kept (the last fine_units ray tiles
+// of each part of the queue): each range's sum in sample order, as the tracer
+// forms it, then the ranges in order, divided by spp.
+__global__ __launch_bounds__(256) void combine_samples_kernel(TraceParams P, Queue Q) {
+    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;  // ray of the samples buffer
+    const long long per_part = 64ll * Q.fine;
+    const int p = (int)(e / per_part);
+    if (p >= kParts) return;
+    const long long r = e - p * per_part, u = r >> 6, c = Q.coarse(p);
+    if (u >= Q.count(p) - c) return;
+    const long long slot = (Q.first(p) + c + u) * 64 + (r & 63);
+    bool none = false;
+    uint32_t k;
+    if (P.views) {
+        const uint32_t t = (uint32_t)(slot >> 6), v = t / (uint32_t)P.vtiles, rem = t - v * (uint32_t)P.vtiles;
+        const uint32_t ty = rem / (uint32_t)P.vtx, tx = rem - ty * (uint32_t)P.vtx;
+        const int py = (int)ty * 8 + (int)((slot >> 3) & 7), px = (int)tx * 8 + (int)(slot & 7);
+        if (py >= P.H || px >= P.W) return;
+        k = (v * (uint32_t)P.H + (uint32_t)py) * (uint32_t)P.W + (uint32_t)px;
+    } else {
+        const int rows = P.row_end - P.row_begin;
+        int ti, tj;
+        tile_coords(slot >> 6, (rows + 7) / 8, (P.N + 7) / 8, ti, tj);
+        const int oi = ti * 8 + (int)((slot >> 3) & 7), dj = tj * 8 + (int)(slot & 7);
+        if (oi >= rows || dj >= P.N) return;
+        const int i = P.perm_o[oi], j = P.perm_d[dj];
+        k = (uint32_t)i * (uint32_t)P.N + (uint32_t)j;
+        none = P.M == P.N && i == j;
+    }
+    f3 acc = mk3(0.0f, 0.0f, 0.0f);
+    if (!none) {
+        const float* s = P.samples + 3 * ((uint64_t)e * (uint32_t)P.spp);
+        for (int q = 0; q < 1 << P.part_log2; ++q) {
+            const int s1 = ((q + 1) * P.spp) >> P.part_log2;
+            f3 sum = mk3(0.0f, 0.0f, 0.0f);
+            for (int i = (q * P.spp) >> P.part_log2; i < s1; ++i) sum = sum + mk3(s[3 * i], s[3 * i + 1], s[3 * i + 2]);
+            acc = q ? acc + sum : sum;
+        }
+        const float fs = (float)P.spp;
+        acc = mk3(acc.x / fs, acc.y / fs, acc.z / fs);
+    }
+    store_texel(P.out, P.dtype, k, acc);
+}
+
 hipError_t launch_combine_parts(const TraceParams& P, hipStream_t s) {
     const long long n = P.views ? (long long)P.nviews * P.H * P.W : (long long)(P.row_end - P.row_begin) * P.N;
     if (n <= 0) return hipSuccess;
-    combine_parts_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(P, n);
+    const Queue Q(ray_tiles(P), P.part_log2, P.fine_units, P.fine_log2);
+    // (texels of kept samples are written last: part_sums has none of theirs)
+    if (P.part_log2 > 0 && Q.part > Q.fine) combine_parts_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(P, n);
+    if (Q.fine > 0) combine_samples_kernel<<<(unsigned)((64ll * Q.fine * kParts + 255) / 256), 256, 0, s>>>(P, Q);
     return hipGetLastError();
 }
 
