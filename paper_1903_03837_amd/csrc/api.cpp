@@ -1,6 +1,7 @@
 // api.cpp -- the C ABI of liblumipath.so (include/lumipath.h): host-side
 // argument validation, parameter packing and kernel launches.  Validation
 // finishes before any HIP call, so a bad argument never touches the device.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -126,11 +127,10 @@ Items work_items(unsigned long long rays, long long ray_tiles, int spp, int log2
     return it;
 }
 Items field_items(const lf_gen_params* p) {
-    if (p->surface) return {};
     const long long re = p->row_end <= 0 ? stored_rows(p) : p->row_end;
     const long long rows = re - p->row_begin;
     return work_items((unsigned long long)rows * (unsigned long long)p->N, (rows + 7) / 8 * ((p->N + 7) / 8), p->spp,
-                      part_log2(p, true));
+                      p->surface ? 0 : part_log2(p, true));
 }
 
 // Cells per axis of the majorant grid in use (0: the global majorant).
@@ -327,10 +327,23 @@ void set_items(lp::TraceParams& T, const Items& items, char* buffer) {
 // Isosurface variant: cells of the raw-range grid (the majorant grid size,
 // 8 when none is set) and their bytes in the workspace.
 int surface_cells(const lf_gen_params* p) { return p->majorant_grid > 0 ? p->majorant_grid : 8; }
-size_t surface_range_bytes(const lf_gen_params* p) {
-    if (!p->surface) return 0;
+// Blocks of the isosurface march: bricks per axis such that no axis has more
+// than 48 (two bits each: 27 KB of LDS), at least two (a block of one brick
+// is crossed in six half-voxel samples).
+constexpr int kMaxBlocks1D = 48;
+int surface_block_bricks(const lf_volume* v) {
+    const int nb = std::max({lp::halo_bricks(v->nx), lp::halo_bricks(v->ny), lp::halo_bricks(v->nz)});
+    return std::max(2, (nb + kMaxBlocks1D - 1) / kMaxBlocks1D);
+}
+int surface_blocks(int n, int bricks) { return (lp::halo_bricks(n) + bricks - 1) / bricks; }
+size_t surface_cells_bytes(const lf_gen_params* p) {
     const size_t G = (size_t)surface_cells(p);
     return align256(8 * G * G * G);
+}
+// (the cells' raw ranges, then the blocks)
+size_t surface_range_bytes(const lf_gen_params* p) {
+    if (!p->surface) return 0;
+    return surface_cells_bytes(p) + align256((size_t)kMaxBlocks1D * kMaxBlocks1D * kMaxBlocks1D / 4);
 }
 
 // Set-up and launch of the isosurface variant; `range` is its workspace.
@@ -359,7 +372,16 @@ hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium
     if (e == hipSuccess)
         e = lp::launch_majorant_grid(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, G, m->lut,
                                      m->lut_size, m->density_scale, vol->vmin, vol->vmax, nullptr, range, s);
+    T.block_bricks = surface_block_bricks(vol);
+    T.inv_block = 1.0f / (float)(3 * T.block_bricks);
+    T.blocks_n[0] = surface_blocks(vol->nx, T.block_bricks);
+    T.blocks_n[1] = surface_blocks(vol->ny, T.block_bricks);
+    T.blocks_n[2] = surface_blocks(vol->nz, T.block_bricks);
+    uint32_t* blocks = (uint32_t*)((char*)range + surface_cells_bytes(p));
+    T.sblocks = blocks;
+    if (e == hipSuccess) e = lp::launch_surface_blocks(T, vol->type, blocks, s);
     if (e == hipSuccess) e = lp::launch_surface(T, vol->type, s);
+    if (e == hipSuccess) e = lp::launch_combine_parts(T, s);
     return e;
 }
 
@@ -463,13 +485,13 @@ int lf_generate(const lf_volume* vol, const lf_medium* eval, const lf_medium* sa
     const lf_medium* sm = sample ? sample : eval;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = lp::launch_halo_bricks(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, (void*)T.vol, s);
+    set_items(T, items, w + gen_order_bytes(params) + brick_copy_bytes(vol) + surface_range_bytes(params));
     if (params->surface) {
         if (e == hipSuccess)
             e = run_surface(T, vol, eval, params, w, (float*)(w + gen_order_bytes(params) + brick_copy_bytes(vol)), s);
         if (e != hipSuccess) return hip_fail(e, "lf_generate (isosurface)");
         return LF_OK;
     }
-    set_items(T, items, w + gen_order_bytes(params) + brick_copy_bytes(vol) + surface_range_bytes(params));
     if (e == hipSuccess) e = setup_tracking(T, vol, sm, params, w, s);
     if (e != hipSuccess) return hip_fail(e, "lf_generate (set-up)");
     const int mode = (sample && sample != eval) ? lp::kFrozen : lp::kFwd;
@@ -544,7 +566,7 @@ int lf_render_views(const lf_volume* vol, const lf_medium* medium, const lf_ligh
     const unsigned long long pixels = (unsigned long long)n_views * (unsigned long long)W * (unsigned long long)H;
     const int vpl = p1.surface ? 0 : view_part_log2(p1.spp, pixels);
     const long long view_tiles = (long long)n_views * ((W + 7) / 8) * ((H + 7) / 8);
-    const Items items = p1.surface ? Items{} : work_items(pixels, view_tiles, p1.spp, vpl);
+    const Items items = work_items(pixels, view_tiles, p1.spp, vpl);
     const size_t need =
         gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1) + items.bytes();
     r = check_workspace(ws, ws_bytes, need);
@@ -579,12 +601,12 @@ int lf_render_views(const lf_volume* vol, const lf_medium* medium, const lf_ligh
     }
     if (e == hipSuccess)
         e = lp::launch_halo_bricks(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, (void*)T.vol, s);
+    set_items(T, items, w + gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1));
     if (p1.surface) {
         if (e == hipSuccess)
             e = run_surface(T, vol, medium, &p1, w,
                             (float*)(w + gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol)), s);
     } else {
-        set_items(T, items, w + gen_order_bytes(&p1) + views_bytes + brick_copy_bytes(vol) + surface_range_bytes(&p1));
         if (e == hipSuccess) e = setup_tracking(T, vol, medium, &p1, w, s);
         if (e == hipSuccess) e = lp::launch_generate_wave(T, vol->type, lp::kFwd, s);
         if (e == hipSuccess) e = lp::launch_combine_parts(T, s);

@@ -80,6 +80,7 @@ hipError_t launch_wave_setup(const TraceParams& P, const float* sample_lut, int 
 hipError_t launch_majorant_grid(const void* vol, int vtype, int layout, int nx, int ny, int nz, int G,
                                 const float* lut, int lut_n, float scale, double vmin, double vmax, float* out,
                                 float* range, hipStream_t s);
+hipError_t launch_surface_blocks(const TraceParams& P, int vtype, uint32_t* out, hipStream_t s);
 hipError_t launch_surface(const TraceParams& P, int vtype, hipStream_t s);
 
 // Up to kViewBatch ground-truth views per argument block.

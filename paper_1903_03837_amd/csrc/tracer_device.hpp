@@ -114,6 +114,11 @@ struct TraceParams {
     int32_t surface;
     float iso, half_voxel;
     const float* srange;
+    // its march's blocks: block_bricks bricks per axis each, blocks_n of them,
+    // two bits per block; inv_block = 1 / (3 block_bricks)
+    int32_t block_bricks, blocks_n[3];
+    float inv_block;
+    const uint32_t* sblocks;
     // ground-truth views (views != nullptr): camera rays instead of the SF ray
     // set, 8 x 8 pixel tiles, stream key = (view * H + y) * W + x
     const ViewCam* views;
@@ -302,8 +307,12 @@ __device__ __forceinline__ void vox_quad(const char* p, float& a0, float& a1, fl
 // for u16, half a line for u8, and one of two lines for f32 (or both, in one
 // case of three).  Its eight voxels sit at fixed offsets from the first, so
 // one 64-bit address serves all loads.
-template <int VT, class PT>
-__device__ __forceinline__ float sample_volume(const PT& P, f3 y) {
+struct VoxelPoint {
+    uint32_t base;      // first voxel of the footprint in the copy
+    float fx, fy, fz;   // position inside it
+};
+template <class PT>
+__device__ __forceinline__ VoxelPoint voxel_point(const PT& P, f3 y) {
     // clamp to [0, n - 1] as one median-of-three
     const float gx = __builtin_amdgcn_fmed3f(fmaf(y.x, P.ga[0], P.gb[0]), 0.0f, P.gmax[0]);
     const float gy = __builtin_amdgcn_fmed3f(fmaf(y.y, P.ga[1], P.gb[1]), 0.0f, P.gmax[1]);
@@ -311,7 +320,6 @@ __device__ __forceinline__ float sample_volume(const PT& P, f3 y) {
     const int ix = min((int)gx, P.imax[0]);
     const int iy = min((int)gy, P.imax[1]);
     const int iz = min((int)gz, P.imax[2]);
-    const float fx = gx - (float)ix, fy = gy - (float)iy, fz = gz - (float)iz;
     // i / 3 as (i * 43691) >> 17, exact for i < 2^17.  Dimensions are below
     // 2^16 and brick counts below 2^15 (stated here so that these products
     // become full-rate 24-bit multiplies); only the last one, whose brick row
@@ -327,15 +335,40 @@ __device__ __forceinline__ float sample_volume(const PT& P, f3 y) {
     const uint32_t brick = (bz * nby + by) * nbx + (bx - bz);
     const uint32_t base = ((((((brick << 2) + ((uint32_t)iz + bz - by)) << 2) + ((uint32_t)iy + by - bx)) << 2)) +
                           ((uint32_t)ix + bx);
+    return {base, gx - (float)ix, gy - (float)iy, gz - (float)iz};
+}
+template <int VT, class PT>
+__device__ __forceinline__ void load_footprint(const PT& P, uint32_t base, float& v000, float& v100, float& v010,
+                                               float& v110, float& v001, float& v101, float& v011, float& v111) {
     constexpr int ESZ = VT == 0 ? 1 : VT == 1 ? 2 : 4;
     const char* const p = (const char*)P.vol + (uint64_t)base * ESZ;
-    float v000, v100, v010, v110, v001, v101, v011, v111;
     vox_quad<VT>(p, v000, v100, v010, v110);
     vox_quad<VT>(p + 16 * ESZ, v001, v101, v011, v111);
-    const float c00 = fmaf(fx, v100 - v000, v000), c10 = fmaf(fx, v110 - v010, v010);
-    const float c01 = fmaf(fx, v101 - v001, v001), c11 = fmaf(fx, v111 - v011, v011);
-    const float c0 = fmaf(fy, c10 - c00, c00), c1 = fmaf(fy, c11 - c01, c01);
-    return fmaf(fz, c1 - c0, c0);
+}
+__device__ __forceinline__ float lerp_footprint(const VoxelPoint& p, float v000, float v100, float v010, float v110,
+                                                float v001, float v101, float v011, float v111) {
+    const float c00 = fmaf(p.fx, v100 - v000, v000), c10 = fmaf(p.fx, v110 - v010, v010);
+    const float c01 = fmaf(p.fx, v101 - v001, v001), c11 = fmaf(p.fx, v111 - v011, v011);
+    const float c0 = fmaf(p.fy, c10 - c00, c00), c1 = fmaf(p.fy, c11 - c01, c01);
+    return fmaf(p.fz, c1 - c0, c0);
+}
+template <int VT, class PT>
+__device__ __forceinline__ float sample_volume(const PT& P, f3 y) {
+    const VoxelPoint p = voxel_point(P, y);
+    float v000, v100, v010, v110, v001, v101, v011, v111;
+    load_footprint<VT>(P, p.base, v000, v100, v010, v110, v001, v101, v011, v111);
+    return lerp_footprint(p, v000, v100, v010, v110, v001, v101, v011, v111);
+}
+// Voxel (x, y, z) of the copy.
+template <int VT, class PT>
+__device__ __forceinline__ float voxel_at(const PT& P, int x, int y, int z) {
+    // (the last voxel of an axis is the fourth of its brick)
+    const int bx = min(x / 3, P.nbx - 1), by = min(y / 3, P.nby - 1), bz = z / 3 - (z == P.nz - 1 && z % 3 == 0 ? 1 : 0);
+    const uint64_t i = 64ull * (((uint64_t)bz * (uint32_t)P.nby + (uint32_t)by) * (uint32_t)P.nbx + (uint32_t)bx) +
+                       (uint32_t)(16 * (z - 3 * bz) + 4 * (y - 3 * by) + (x - 3 * bx));
+    if constexpr (VT == 0) return (float)((const uint8_t*)P.vol)[i];
+    else if constexpr (VT == 1) return (float)((const uint16_t*)P.vol)[i];
+    else return ((const float*)P.vol)[i];
 }
 
 struct TF {
