@@ -317,12 +317,13 @@ int lf_majorant_grid(const lf_volume* vol, const lf_medium* sample, const lf_gen
 /* Adjoint of lf_generate (path-replay extension): given d_lf = d(loss)/d(Lhat)
  * (float32 [origin_rows][N][3]), overwrites d_lut (float32 [lut_size][4]) and d_scale
  * (float32 [1]) with d(loss)/d(LUT) and d(loss)/d(density_scale) of the
- * estimator for the same random stream, majorant held fixed.  Each sample is
- * traced twice (total radiance, then scores times radiance gathered after
- * each event); nothing is stored per path.  With params->sample_radiance
- * (the samples' radiance kept by lf_generate) the first trace is skipped.  Accumulation uses float atomics:
- * reproducible to rounding only.  Rows with zero adjoint are skipped.
- * Workspace as for lf_generate. */
+ * estimator for the same random stream, majorant held fixed.  An event's
+ * score times the radiance gathered after it: a path's events are kept in the
+ * workspace (1 KiB for each lane of the launch, at most 192 MiB) until its
+ * radiance is known, and a path with more events is traced a second time.
+ * With params->sample_radiance (the samples' radiance kept by lf_generate)
+ * only shadow rays' events are kept.  Accumulation uses float atomics:
+ * reproducible to rounding only.  Rows with zero adjoint are skipped. */
 int lf_generate_backward(const lf_volume* vol, const lf_medium* medium, const lf_light* light,
                          const lf_gen_params* params, const float* d_lf, float* d_lut,
                          float* d_scale, void* ws, size_t* ws_bytes, void* stream);

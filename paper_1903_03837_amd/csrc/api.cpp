@@ -715,7 +715,11 @@ int lf_generate_backward(const lf_volume* vol, const lf_medium* medium, const lf
     // then the brick copy of the volume
     const long long re = params->row_end <= 0 ? stored_rows(params) : params->row_end;
     const size_t list_bytes = align256(4 * (size_t)(re - params->row_begin) * (size_t)params->N);
-    const size_t need = gen_order_bytes(params) + list_bytes + brick_copy_bytes(vol) + kCtrBytes;
+    // (and the lanes' event records)
+    const long long chunks = ((re - params->row_begin + 7) / 8 * ((params->N + 7) / 8)) << part_log2(params, false);
+    const int groups = (int)std::min<long long>(lp::kRecordGroups, std::max(1ll, (chunks + 3) / 4));
+    const size_t fixed = gen_order_bytes(params) + list_bytes + brick_copy_bytes(vol) + kCtrBytes;
+    const size_t need = fixed + sizeof(float4) * lp::kRecords * 256 * (size_t)groups;
     r = check_workspace(ws, ws_bytes, need);
     if (r == 1) {
         *ws_bytes = need;
@@ -735,6 +739,8 @@ int lf_generate_backward(const lf_volume* vol, const lf_medium* medium, const lf
     T.vol = w + gen_order_bytes(params) + list_bytes;
     T.tile_ctr = (unsigned int*)(w + gen_order_bytes(params) + list_bytes + brick_copy_bytes(vol));
     T.ctr_stride = kCtrStride;
+    T.records = (float4*)(w + fixed);
+    T.record_groups = groups;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = lp::launch_halo_bricks(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, (void*)T.vol, s);
     if (e == hipSuccess) e = lp::launch_zero(d_lut, 4ll * medium->lut_size, s);

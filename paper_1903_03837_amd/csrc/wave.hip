@@ -37,13 +37,28 @@
 //
 // Adjoint mode: the rays with a nonzero adjoint are first compacted into a
 // list (in the same spatial order) and the waves take 64-ray chunks of that
-// list.  Every sample runs twice: pass A gathers its radiance L_tot, pass B
-// replays the same stream and, at every event, adds the event's score times
-// the radiance gathered after it (adjoint . (L_tot - L_so_far)) to per-
-// workgroup LDS gradients: real collision d sigma / sigma, null collision and
-// ratio-tracking step -d sigma / (sigma_bar - sigma), albedo d rho / rho.  A
-// shadow ray in pass B runs twice (transmittance first, then its scores,
-// which multiply only its own NEE term).  Nothing is stored per path.
+// list.  An event's score times the radiance gathered after it (adjoint .
+// (L_tot - L_so_far)) is added to per-workgroup LDS gradients: real collision
+// d sigma / sigma, null collision and ratio-tracking step -d sigma /
+// (sigma_bar - sigma) (a shadow ray's steps multiply only its own light
+// sample's term), albedo d rho / rho.  That radiance is known only at the
+// path's end, so a path's events are recorded as they happen and scored
+// afterwards: up to kRecords of 16 bytes per lane (in memory; LDS has room for
+// an eighth of them), one per block (its two points' raw values and their
+// scores' divisors) and one per vertex (its light sample's contribution and
+// the number of its shadow ray's records).  Lanes whose path is done wait
+// until a quarter of the wave does; then the wave scores their lists as one,
+// 64 records at a time, a lane each.  A path with more records is traced
+// again with its radiance known, its flights scored as they happen, and so is
+// every sample whose radiance the forward kept; a shadow ray's steps are then
+// recorded in the same way, and traced again if they are too many.
+// The tracing bounds it, as it does the forward.  128^3 f32, N = 1024, 32 spp
+// (10 events per sample, 7.5 of them in shadow rays), the training step:
+// 19.2 ms when every sample was traced a second time and its shadow rays a
+// third, 18.1 when each lane scored its own list (a quarter of the lanes
+// busy), 15.3 when the lists are shared, 14.4 at three waves per SIMD; 11.6
+// with the scoring left out.  Several copies of the LDS sums against
+// conflicting atomics: no difference.
 #include "internal.hpp"
 
 namespace lp {
@@ -53,13 +68,13 @@ namespace lp {
 // (pinhole rays of pixel tiles) instead of light-field rays, also a separate
 // instantiation so that the light-field kernel carries none of its code.
 // Registers are budgeted for four resident waves per SIMD (128 VGPRs; frozen
-// sampling and the adjoint spill a few values).  Other budgets measured: five
+// sampling spills a few values), the adjoint's for three (166, where four
+// spilled 33 values: the training step took 15.3 instead of 14.4 ms).  Other budgets measured: five
 // waves (96) take the 256^3 u16 step from 58 to 71 ms and views from 17.3 to
 // 20.6 ms; three resident waves take the 512^3 field at N = 32768 from 152 to
-// 167 ms per 2048 rows, and the adjoint of a dense 128^3 training pass from
-// 17.4 to 17.8 ms.
+// 167 ms per 2048 rows.
 template <int VT, int MODE, bool STATS, bool VIEWS>
-__global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
+__global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(TraceParams P) {
     // LDS: cell majorants and their reciprocals (first, so that the grid walk's
     // byte offsets are its addresses), then the tables
     extern __shared__ float4 smem[];
@@ -119,7 +134,8 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
     float W = 1.0f, t = 0.0f, tend = 0.0f, Tr = 1.0f, up0 = 0.0f, up1 = 0.0f;
     f3 isd = po;  // reciprocals of the current segment's direction (dir or om)
     Counters cnt = {0, 0, 0, 0, 0};
-    // adjoint state: texel adjoint / spp, pass A radiance, pass, NEE score weight
+    // adjoint state: texel adjoint / spp, the sample's radiance, pass (0: radiance not known yet, 1: known,
+    // scored on the way, 2: whole path recorded), score weight of the light sample
     f3 adj = po, ltot = po;
     int pass = 0;
     float rc = 0.0f;
@@ -128,6 +144,11 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
     G.cl0 = -1;
     G.c0 = G.c1 = 0.0f;
     G.dscale = 0.0f;
+    // recorded events: nrec of them, `heads` the vertices among them (bit per
+    // record), `mark` the latest vertex
+    int nrec = 0, mark = 0;
+    uint64_t heads = 0;
+    const uint32_t rec_at = ((uint32_t)blockIdx.x * 256u + threadIdx.x) * (uint32_t)kRecords;
 
     KTraceParams* Pk = (KTraceParams*)__builtin_amdgcn_kernarg_segment_ptr();
     for (;;) {
@@ -150,13 +171,16 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
         if (mode == kDone) {
             bool next = true;
             if constexpr (MODE == kGrad) {
-                if (pass == 0) {  // replay the same sample with scores
+                if (pass == 0) {  // radiance known: score the recorded events
                     ltot = L;
-                    pass = 1;
-                    next = false;
-                } else {
-                    pass = P.srad ? 1 : 0;
+                    next = nrec == 0;
+                    pass = 1;  // (too many to keep: replay the sample with scores)
+                    if (nrec > 0 && nrec <= kRecords) {
+                        pass = 2;
+                        mode = kScore;
+                    }
                 }
+                if (next) pass = P.srad ? 1 : 0;
             } else {
                 acc = acc + L;
                 if (P.srad && !VIEWS) {
@@ -187,7 +211,7 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     }
                 }
                 mode = kIdle;
-            } else {
+            } else if (MODE != kGrad || mode != kScore) {
                 mode = kStart;
                 b = 0;
                 blk = 0;
@@ -331,6 +355,78 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
             continue;
         }
 
+        // ------------------------------------------------------------- score
+        if constexpr (MODE == kGrad) {
+            const int scoring = __popcll(__ballot(mode == kScore));
+            if (scoring != 0 && scoring * 64 >= kScoreLanes * live) {
+                // the lanes' lists as one, 64 records at a time
+                const int mine = mode == kScore ? nrec : 0;
+                int end = mine;  // inclusive prefix sum
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int v = __shfl_up(end, o, 64);
+                    end += lane >= o ? v : 0;
+                }
+                const int total = __builtin_amdgcn_readlane(end, 63);
+                const uint32_t wave_at = rec_at - (uint32_t)lane * (uint32_t)kRecords;
+                for (int first = 0; first < total; first += 64) {
+                    const int g = first + lane;
+                    // the list that holds record g: the number of lists that end at or before it
+                    int own = 0;
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1)
+                        if (__shfl(end, own + o - 1, 64) <= g) own += o;
+                    own = min(own, 63);
+                    const int at = g - (__shfl(end, own, 64) - __shfl(mine, own, 64));
+                    const f3 adj1 = mk3(__shfl(adj.x, own, 64), __shfl(adj.y, own, 64), __shfl(adj.z, own, 64));
+                    const f3 ltot1 = mk3(__shfl(ltot.x, own, 64), __shfl(ltot.y, own, 64), __shfl(ltot.z, own, 64));
+                    const uint64_t heads1 = (uint64_t)__shfl((uint32_t)heads, own, 64) |
+                                            (uint64_t)__shfl((uint32_t)(heads >> 32), own, 64) << 32;
+                    const float rc1 = __shfl(rc, own, 64);
+                    const bool path = __shfl(pass, own, 64) == 2;  // a whole path (else a shadow ray only)
+                    if (g < total && !((heads1 >> at) & 1)) {
+                        const float4* const list =
+                            (const float4*)((const char*)P.records + (wave_at + (uint32_t)own * (uint32_t)kRecords) * 16u);
+                        const float4 q = list[at];
+                        // the radiance gathered before the record, and whether a shadow ray's
+                        f3 L1 = mk3(0.0f, 0.0f, 0.0f);
+                        bool shadow = !path;
+                        float gain = rc1;
+                        for (uint64_t hs = heads1 & ((1ull << at) - 1ull); hs; hs &= hs - 1) {
+                            const int h = __ffsll((long long)hs) - 1;
+                            const float4 v = list[h];
+                            L1 = L1 + mk3(v.x, v.y, v.z);
+                            shadow = at <= h + __float_as_int(v.w);
+                            gain = dot(adj1, mk3(v.x, v.y, v.z));
+                        }
+                        const bool on = !shadow || gain != 0.0f;
+                        if (!shadow) gain = dot(adj1, ltot1 - L1);
+                        const bool inA = __float_as_uint(q.y) != kNoPoint, inB = __float_as_uint(q.w) != kNoPoint;
+                        const TF fA = classify<MODE>(P, lut_e, lut_s, q.x), fB = classify<MODE>(P, lut_e, lut_s, q.z);
+                        if (on && inA) G.sigma(fA, P.scale_e, gain / q.y);
+                        if (on && inB) G.sigma(fB, P.scale_e, gain / q.w);
+                        if (at < kRecords - 1 && ((heads1 >> (at + 1)) & 1)) {  // its last point is a real collision
+                            TF te;
+                            te.l0 = inB ? fB.l0 : fA.l0;
+                            te.w = inB ? fB.w : fA.w;
+                            G.albedo(te, tf_rgb(lut_e, te), (ltot1 - L1) * adj1);
+                        }
+                    }
+                }
+                if (mode == kScore) {
+                    mode = kDone;
+                    if (pass == 1) {  // the shadow ray's light, and the path goes on
+                        L = L + C * Tr;
+                        if (b != P.maxb - 1) {
+                            ++b;
+                            blk = 0;
+                            mode = kScatter;
+                        }
+                    }
+                }
+            }
+        }
+
         // Passes: the first one draws a block for every lane and runs the
         // set-up of START, SCATTER and VERTEX lanes; further passes, while at
         // least kTrackPass lanes are still tracking a segment, advance only
@@ -398,6 +494,8 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                         ua = u01(r.y);
                         T = mk3(1.0f, 1.0f, 1.0f);
                         W = 1.0f;
+                        nrec = 0;
+                        heads = 0;
                         L = mk3(0.0f, 0.0f, 0.0f);
                     } else {
                         const float mu = hg_mu(P.g, up0);
@@ -432,6 +530,7 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                             tend = te;
                             mode = kShadow;
                             blk = 1;
+                            if (pass) nrec = 0;
                         } else {
                             L = L + C;
                             after_shadow = true;
@@ -506,8 +605,17 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     // (sigma_bar - sigma) at a null one and at a shadow step
                     const bool on = flight ? pass != 0 : mode == kShadow2;
                     const float gain = flight ? dot(adj, ltot - L) : rc;
-                    if (on && inA) G.sigma(fA, P.scale_e, (realA ? gain : -gain) / (realA ? sgA : sbA - sgA));
-                    if (on && inB) G.sigma(fB, P.scale_e, (realB ? gain : -gain) / (realB ? sgB : sbB - sgB));
+                    const float divA = realA ? sgA : sgA - sbA, divB = realB ? sgB : sgB - sbB;
+                    if (on && inA) G.sigma(fA, P.scale_e, gain / divA);
+                    if (on && inB) G.sigma(fB, P.scale_e, gain / divB);
+                    // where the factor is not known yet, the points are recorded
+                    if ((pass == 0 || mode == kShadow) && (inA || inB)) {
+                        if (nrec < kRecords)
+                            *(float4*)((char*)P.records + (rec_at + (uint32_t)nrec) * 16u) =
+                                make_float4(rawA, inA ? divA : __uint_as_float(kNoPoint), rawB,
+                                            inB ? divB : __uint_as_float(kNoPoint));
+                        ++nrec;
+                    }
                 }
                 if (ev_end) {
                     if (mode == kFlight) {
@@ -516,7 +624,10 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     } else if (MODE == kGrad && mode == kShadow && pass) {
                         // transmittance known: replay the shadow ray for its scores
                         rc = dot(adj, C * Tr);
-                        if (rc != 0.0f) {
+                        if (rc != 0.0f && nrec > 0 && nrec <= kRecords) {
+                            mode = kScore;
+                            heads = 0;
+                        } else if (rc != 0.0f && nrec > 0) {
                             mode = kShadow2;
                             blk = 1;
                             t = 0.0f;
@@ -525,6 +636,10 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                             after_shadow = true;
                         }
                     } else {
+                        if constexpr (MODE == kGrad)
+                            if (mode == kShadow && mark < kRecords)  // the vertex's record
+                                *(float4*)((char*)P.records + (rec_at + (uint32_t)mark) * 16u) = make_float4(
+                                    C.x * Tr, C.y * Tr, C.z * Tr, __int_as_float(nrec - mark - 1));
                         L = L + C * Tr;
                         after_shadow = true;
                     }
@@ -536,17 +651,14 @@ __global__ __launch_bounds__(256, 4) void gen_wave_kernel(TraceParams P) {
                     const f3 rgb = tf_rgb(lut_e, te);
                     if constexpr (MODE == kGrad) {
                         if (pass) {
-                            // albedo scores d rho_c / rho_c times the channel's later radiance
-                            const f3 after = (ltot - L) * adj;
-                            const float ra[3] = {rgb.x, rgb.y, rgb.z};
-                            const float af[3] = {after.x, after.y, after.z};
-#pragma unroll
-                            for (int c = 0; c < 3; ++c)
-                                if (ra[c] > 0.0f && ra[c] < 1.0f && af[c] != 0.0f) {
-                                    const float f = af[c] / ra[c];
-                                    atomicAdd(&glds[te.l0 * 4 + c], f * (1.0f - te.w));
-                                    atomicAdd(&glds[te.l0 * 4 + 4 + c], f * te.w);
-                                }
+                            G.albedo(te, rgb, (ltot - L) * adj);
+                        } else {
+                            if (nrec < kRecords) {
+                                heads |= 1ull << nrec;
+                                *(float4*)((char*)P.records + (rec_at + (uint32_t)nrec) * 16u) =
+                                    make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            }
+                            mark = nrec++;
                         }
                     }
                     x = realB ? yB : yA;
@@ -758,6 +870,7 @@ static hipError_t launch_wave_t(const TraceParams& P, hipStream_t s) {
                                                          lds);
     if (e != hipSuccess) return e;
     long long blocks = (long long)cus * (per_cu > 0 ? per_cu : 1);
+    if (MODE == kGrad && blocks > P.record_groups) blocks = P.record_groups;
     // at least one tile per wave (list lengths are only known on the device;
     // waves that find no chunk exit at once)
     const long long need = (ntiles + 3) / 4;
