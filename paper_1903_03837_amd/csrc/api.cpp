@@ -407,8 +407,6 @@ hipError_t setup_tracking(lp::TraceParams& T, const lf_volume* vol, const lf_med
     T.tab_d = tab_d;
     hipError_t e = lp::launch_wave_setup(T, sm->lut, sm->lut_size, sm->density_scale, p->majorant, sig, perm_o,
                                          perm_d, s);
-    if (e == hipSuccess) e = lp::launch_sf_table(p->M, 1.0f / (float)p->M, tab_o, s);
-    if (e == hipSuccess) e = lp::launch_sf_table(p->N, 1.0f / (float)p->N, tab_d, s);
     if (e == hipSuccess && grid_cells(p) > 0) {
         float* cells = (float*)(w + gen_perm_bytes(p));
         T.maj = cells;

@@ -107,7 +107,5 @@ constexpr int kMaxScratchDevices = 64;
 hipError_t lookup_scratch(int dev, void** ptr);
 hipError_t launch_sf_tables(const LookupParams& P, hipStream_t s);
 hipError_t launch_combine_parts(const TraceParams& P, hipStream_t s);
-// Table of the n SF points sf_point(n, i, inv_n) as float4 (w = 0).
-hipError_t launch_sf_table(int n, float inv_n, float4* out, hipStream_t s);
 
 }  // namespace lp

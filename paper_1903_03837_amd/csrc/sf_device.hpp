@@ -79,6 +79,13 @@ __device__ __forceinline__ f3 sf_point(int n, int i, float inv_n) {
     return {c * st, s * st, z};
 }
 
+// Entry i of an SF set's point table (float4 per point, w = 0).
+__device__ __forceinline__ void sf_table_entry(int n, float inv_n, float4* t, uint32_t i) {
+    if (i >= (uint32_t)n) return;
+    const f3 p = sf_point(n, (int)i, inv_n);
+    t[i] = make_float4(p.x, p.y, p.z, 0.0f);
+}
+
 // Lattice basis of zone k of an SF set of n points in (azimuth, height): the
 // index steps F(k) and F(k+1) move by (b00, b10) and (b01, b11); inv_det is
 // the inverse of the basis determinant; f_km1, f_k, f_kp1 are the Fibonacci

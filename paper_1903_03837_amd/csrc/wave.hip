@@ -723,28 +723,6 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
     }
 }
 
-// Spatial order of count consecutive SF indices base..base+count-1 of a set
-// of n points: bands of B indices, each sorted by azimuth (rank counting).
-// One workgroup per band, its azimuths staged in LDS (B <= 1272 for
-// n <= 65535).
-constexpr int kMaxBand = 1280;
-__global__ __launch_bounds__(256) void sf_order_kernel(int base, int count, int band, int32_t* out) {
-    __shared__ float fr[kMaxBand];
-    const int lo = blockIdx.x * band;
-    const int cnt = min(count - lo, band);
-    for (int t = (int)threadIdx.x; t < cnt; t += 256) fr[t] = sf_frac(base + lo + t);
-    __syncthreads();
-    for (int t = (int)threadIdx.x; t < cnt; t += 256) {
-        const float fe = fr[t];
-        int rank = 0;
-        for (int f = 0; f < cnt; ++f) {
-            const float ff = fr[f];
-            rank += ff < fe || (ff == fe && f < t);
-        }
-        out[lo + rank] = base + lo + t;
-    }
-}
-
 // Compacts the rays (in the spatial tile order) whose adjoint is nonzero and
 // which can reach the volume box (a ray that misses it in every sample has no
 // collision and so no score).
@@ -799,20 +777,72 @@ __global__ __launch_bounds__(256) void active_rays_kernel(TraceParams P) {
     }
 }
 
-__global__ void wave_setup_kernel(const float* lut, int n, float scale, float given, float* sigbar,
-                                  unsigned int* ctr, int ctr_stride, unsigned int* ray_count) {
-    __shared__ float red[256];
+// What the persistent kernels need beside the volume, in one launch: the
+// global majorant and the cleared counters (the last workgroup), the spatial
+// orders of origin rows and directions (one workgroup per band) and both
+// point tables.  Each part is latency: as five launches they were 7 % of a
+// small field's call (256 x 256 rays, 16 spp, 64^3: 0.53 ms).
+struct SetupParams {
+    const float* lut;
+    int lut_n;
+    float scale, given;
+    float* sigbar;
+    unsigned int *ctr, *ray_count;
+    int ctr_stride;
+    // order and table of the origin rows and of the directions
+    struct Set {
+        int base, count, band;  // indices ordered, in bands
+        int32_t* perm;
+        int n;                  // points of the set
+        float inv_n;
+        float4* table;
+        unsigned order_groups, table_groups;
+    } set[2];
+};
+
+// Spatial order of count consecutive SF indices base..base+count-1 of a set
+// of n points: bands of B indices, each sorted by azimuth (rank counting).
+// One workgroup per band, its azimuths staged in LDS (B <= 1272 for
+// n <= 65535).
+constexpr int kMaxBand = 1280;
+__device__ __forceinline__ void order_band(const SetupParams::Set& S, unsigned group, float* fr) {
+    const int lo = (int)group * S.band;
+    const int cnt = min(S.count - lo, S.band);
+    for (int t = (int)threadIdx.x; t < cnt; t += 256) fr[t] = sf_frac(S.base + lo + t);
+    __syncthreads();
+    for (int t = (int)threadIdx.x; t < cnt; t += 256) {
+        const float fe = fr[t];
+        int rank = 0;
+        for (int f = 0; f < cnt; ++f) {
+            const float ff = fr[f];
+            rank += ff < fe || (ff == fe && f < t);
+        }
+        S.perm[lo + rank] = S.base + lo + t;
+    }
+}
+
+__global__ __launch_bounds__(256) void setup_kernel(SetupParams P) {
+    __shared__ float lds[kMaxBand];
+    unsigned g = blockIdx.x;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const SetupParams::Set& S = P.set[a];
+        if (g < S.order_groups) return order_band(S, g, lds);
+        g -= S.order_groups;
+        if (g < S.table_groups) return sf_table_entry(S.n, S.inv_n, S.table, g * 256u + threadIdx.x);
+        g -= S.table_groups;
+    }
     float m = 0.0f;
-    for (int e = threadIdx.x; e < n; e += 256) m = fmaxf(m, lut[4 * e + 3]);
-    red[threadIdx.x] = m;
-    if (threadIdx.x < kParts) ctr[threadIdx.x * ctr_stride] = 0u;
-    if (threadIdx.x == kParts && ray_count) *ray_count = 0u;
+    for (int e = threadIdx.x; e < P.lut_n; e += 256) m = fmaxf(m, P.lut[4 * e + 3]);
+    lds[threadIdx.x] = m;
+    if (threadIdx.x < kParts) P.ctr[threadIdx.x * P.ctr_stride] = 0u;
+    if (threadIdx.x == kParts && P.ray_count) *P.ray_count = 0u;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
+        if ((int)threadIdx.x < w) lds[threadIdx.x] = fmaxf(lds[threadIdx.x], lds[threadIdx.x + w]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) sigbar[0] = given > 0.0f ? given : 1.25f * scale * red[0];
+    if (threadIdx.x == 0) P.sigbar[0] = P.given > 0.0f ? P.given : 1.25f * P.scale * lds[0];
 }
 
 static int band_size(int n) {
@@ -823,12 +853,19 @@ static int band_size(int n) {
 
 hipError_t launch_wave_setup(const TraceParams& P, const float* sample_lut, int lut_n, float sample_scale,
                              float given, float* sigbar, int32_t* perm_o, int32_t* perm_d, hipStream_t s) {
-    wave_setup_kernel<<<1, 256, 0, s>>>(sample_lut, lut_n, sample_scale, given, sigbar, P.tile_ctr, P.ctr_stride,
-                                        P.ray_count);
+    SetupParams S = {sample_lut, lut_n, sample_scale, given, sigbar, P.tile_ctr, P.ray_count, P.ctr_stride, {}};
     const int rows = P.row_end - P.row_begin;
-    const int bo = band_size(P.M), bd = band_size(P.N);
-    if (rows > 0) sf_order_kernel<<<(rows + bo - 1) / bo, 256, 0, s>>>(P.row_begin, rows, bo, perm_o);
-    sf_order_kernel<<<(P.N + bd - 1) / bd, 256, 0, s>>>(0, P.N, bd, perm_d);
+    auto fill = [](int base, int count, int n, int32_t* perm, const float4* table) {
+        SetupParams::Set t = {base, count, band_size(n), perm, n, 1.0f / (float)n, (float4*)table, 0, 0};
+        if (count > 0) t.order_groups = (unsigned)((count + t.band - 1) / t.band);
+        if (table) t.table_groups = (unsigned)(n + 255) / 256;
+        return t;
+    };
+    S.set[0] = fill(P.row_begin, rows, P.M, perm_o, P.tab_o);
+    S.set[1] = fill(0, P.N, P.N, perm_d, P.tab_d);
+    unsigned groups = 1;
+    for (const auto& t : S.set) groups += t.order_groups + t.table_groups;
+    setup_kernel<<<groups, 256, 0, s>>>(S);
     return hipGetLastError();
 }
 
