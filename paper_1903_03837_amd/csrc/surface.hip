@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256, 4) void surface_kernel(TraceParams P) {
         if (mode == kSDone) {
             acc = acc + L;
             if (part < 0) {
-                float* o = P.samples + 3 * ((uint64_t)(part & 0x7fffffff) * (uint32_t)P.spp + (uint32_t)s);
+                float* o = kept_sample(P, part & 0x7fffffff, s);
                 o[0] = L.x;
                 o[1] = L.y;
                 o[2] = L.z;
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256, 4) void surface_kernel(TraceParams P) {
                         acc = acc + env;
                         cnt.samples++;
                         if (fine) {
-                            float* o = P.samples + 3 * ((uint64_t)(part & 0x7fffffff) * (uint32_t)P.spp + (uint32_t)s);
+                            float* o = kept_sample(P, part & 0x7fffffff, s);
                             o[0] = env.x;
                             o[1] = env.y;
                             o[2] = env.z;

@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
                     o[2] = L.z;
                 }
                 if (part < 0) {
-                    float* o = P.samples + 3 * ((uint64_t)(part & 0x7fffffff) * (uint32_t)P.spp + (uint32_t)s);
+                    float* o = kept_sample(P, part & 0x7fffffff, s);
                     o[0] = L.x;
                     o[1] = L.y;
                     o[2] = L.z;
@@ -323,11 +323,11 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
                         if constexpr (MODE != kGrad) {
                             if (misses_box(P, O, bmin, bmax, po, d0)) {
                                 if (fine) {  // all of the item's samples
-                                    float* o = P.samples + 3 * ((uint64_t)(part & 0x7fffffff) * (uint32_t)P.spp);
                                     for (int s2 = s_first; s2 < s_end; ++s2) {
-                                        o[3 * s2 + 0] = env.x;
-                                        o[3 * s2 + 1] = env.y;
-                                        o[3 * s2 + 2] = env.z;
+                                        float* o = kept_sample(P, part & 0x7fffffff, s2);
+                                        o[0] = env.x;
+                                        o[1] = env.y;
+                                        o[2] = env.z;
                                     }
                                     // (of the kept sample radiance, the last one of each range)
                                     if (P.srad && ((item + 1) & ((1 << (lg - plog)) - 1)) == 0) {
@@ -982,11 +982,13 @@ __global__ __launch_bounds__(256) void combine_samples_kernel(TraceParams P, Que
     }
     f3 acc = mk3(0.0f, 0.0f, 0.0f);
     if (!none) {
-        const float* s = P.samples + 3 * ((uint64_t)e * (uint32_t)P.spp);
+        const float* s = kept_sample(P, (uint32_t)e, 0);
         for (int q = 0; q < 1 << P.part_log2; ++q) {
             const int s1 = ((q + 1) * P.spp) >> P.part_log2;
             f3 sum = mk3(0.0f, 0.0f, 0.0f);
-            for (int i = (q * P.spp) >> P.part_log2; i < s1; ++i) sum = sum + mk3(s[3 * i], s[3 * i + 1], s[3 * i + 2]);
+#pragma unroll 8
+            for (int i = (q * P.spp) >> P.part_log2; i < s1; ++i)
+                sum = sum + mk3(s[192 * i], s[192 * i + 1], s[192 * i + 2]);
             acc = q ? acc + sum : sum;
         }
         const float fs = (float)P.spp;
