@@ -14,7 +14,7 @@ oracle on a seeded 1 % ray subset), the CT-like step with the adjoint
 lookup fused with an L2 loss gradient and its transpose, path-replay adjoint;
 only rays the views reach carry an adjoint), and the dense adjoint of the
 differentiation workload (128^3 f32, N = 1024, 32 spp: every ray carries an
-adjoint, two replays per sample).  One JSON line on stdout; progress on
+adjoint, nothing kept from the forward).  One JSON line on stdout; progress on
 stderr.  Inputs are seeded synthetic data (lfsynth).
 """
 import argparse
@@ -382,8 +382,8 @@ def c2_step_extra(steps, warmup):
 
 def c5_dense_adjoint():
     """Differentiation workload: forward, and the adjoint with every
-    non-degenerate ray carrying a (seeded) adjoint value: two replays per
-    sample, nothing kept from the forward."""
+    non-degenerate ray carrying a (seeded) adjoint value, nothing kept from
+    the forward."""
     import numpy as np
     import torch
 
