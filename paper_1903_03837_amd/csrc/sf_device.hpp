@@ -69,20 +69,26 @@ __device__ __forceinline__ float sf_frac(int i) {
     double f = (double)i * kPhiM1;
     return (float)(f - floor(f));
 }
-__device__ __forceinline__ f3 sf_point(int n, int i, float inv_n) {
+__device__ __forceinline__ f3 sf_point_at(int n, int i, float inv_n, float frac) {
     float s, c;
-    sincospif(2.0f * sf_frac(i), &s, &c);
+    sincospif(2.0f * frac, &s, &c);
     const uint32_t a = 2u * (uint32_t)i + 1u;
     const uint32_t b = 2u * (uint32_t)n - a;
     const float st = sqrtf((float)((uint64_t)a * b)) * inv_n;
     const float z = (float)(n - 2 * i - 1) * inv_n;
     return {c * st, s * st, z};
 }
+__device__ __forceinline__ f3 sf_point(int n, int i, float inv_n) { return sf_point_at(n, i, inv_n, sf_frac(i)); }
 
-// Entry i of an SF set's point table (float4 per point, w = 0).
+// Entry i of an SF set's point table (float4 per point, w = 0).  The product
+// is rounded before its fraction is taken, in every file (fused, as where
+// contraction is on, one of 32768 azimuths is an ulp off): generation and
+// lookup tables and the points a caller is given are the same.
 __device__ __forceinline__ void sf_table_entry(int n, float inv_n, float4* t, uint32_t i) {
+#pragma clang fp contract(off)
     if (i >= (uint32_t)n) return;
-    const f3 p = sf_point(n, (int)i, inv_n);
+    const double f = (double)(int)i * kPhiM1;
+    const f3 p = sf_point_at(n, (int)i, inv_n, (float)(f - floor(f)));
     t[i] = make_float4(p.x, p.y, p.z, 0.0f);
 }
 
