@@ -264,8 +264,8 @@ __global__ __launch_bounds__(256, 4) void surface_kernel(TraceParams P) {
             if (q >= 0) {
                 const long long slot = q >> lg;
                 const int item = (int)q & ((1 << lg) - 1);
-                s = (item * P.spp) >> lg;
-                s_end = ((item + 1) * P.spp) >> lg;
+                s = item_sample(item, P.spp, lg);
+                s_end = item_sample(item + 1, P.spp, lg);
                 part = fine ? (int)(0x80000000u | (uint32_t)(slot + shift)) : 0;
                 bool active = false;
                 int skip = 0;  // environment samples at the item's start

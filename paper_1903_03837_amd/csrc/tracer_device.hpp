@@ -193,6 +193,14 @@ __device__ __forceinline__ float* kept_sample(const PT& P, uint32_t r, int s) {
     return P.samples + 3 * (((uint64_t)(r >> 6) * (uint32_t)P.spp + (uint32_t)s) * 64 + (r & 63));
 }
 
+// First sample of item `item` of the 2^log2 that a ray's spp samples are split
+// into (the item ends where the next begins).  The product is formed in 64
+// bits: finely split rays have up to spp items, and 32 bits overflow from 65536
+// samples on.
+__host__ __device__ __forceinline__ int item_sample(int item, int spp, int log2) {
+    return (int)(((long long)item * spp) >> log2);
+}
+
 // The work queue: `units` in kParts contiguous parts of equal length.  A unit
 // is a ray tile (64 rays), of which each part hands out the first ones with
 // 2^log2 items per ray and the last `fine` ones with 2^fine_log2 (in the

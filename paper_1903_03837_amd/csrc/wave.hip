@@ -257,8 +257,8 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
                 // work item q: sample range q mod 2^lg of ray slot q >> lg
                 const long long slot = q >> lg;
                 const int item = (int)q & ((1 << lg) - 1);
-                const int s_first = (item * P.spp) >> lg;
-                s_end = ((item + 1) * P.spp) >> lg;
+                const int s_first = item_sample(item, P.spp, lg);
+                s_end = item_sample(item + 1, P.spp, lg);
                 part = fine ? (int)(0x80000000u | (uint32_t)(slot + shift)) : item;
                 if constexpr (MODE == kGrad) {
                     if (q < nlist) {
@@ -984,10 +984,10 @@ __global__ __launch_bounds__(256) void combine_samples_kernel(TraceParams P, Que
     if (!none) {
         const float* s = kept_sample(P, (uint32_t)e, 0);
         for (int q = 0; q < 1 << P.part_log2; ++q) {
-            const int s1 = ((q + 1) * P.spp) >> P.part_log2;
+            const int s1 = item_sample(q + 1, P.spp, P.part_log2);
             f3 sum = mk3(0.0f, 0.0f, 0.0f);
 #pragma unroll 8
-            for (int i = (q * P.spp) >> P.part_log2; i < s1; ++i)
+            for (int i = item_sample(q, P.spp, P.part_log2); i < s1; ++i)
                 sum = sum + mk3(s[192 * i], s[192 * i + 1], s[192 * i + 2]);
             acc = q ? acc + sum : sum;
         }
