@@ -96,7 +96,9 @@ constexpr size_t kCtrBytes = 4 * kCtrStride * lp::kParts;
 // and summed by a second kernel in the same order (same bits).  They make up
 // four ordinary items of every lane of the full grid (2^18 lanes), enough to
 // fill the gaps that the longest ordinary items leave, and at most 2^25
-// samples (403 MB).  Below 8 samples per ray there is little to split.
+// samples (403 MB): from 65537 samples per ray on, one tile of each part would
+// pass that, and nothing is split.  Below 8 samples per ray there is little to
+// split.
 // Measured: 256^3 step 58.0 -> 53.0 ms (two items per lane instead of four
 // 55.5, eight 53.4; one or four samples per item 53.5), views at 256 spp 17.1
 // -> 15.5 ms, 128^3 training pass 18.7 -> 18.1 ms; 64^3, N = 256, 16 spp 1.18
@@ -115,7 +117,7 @@ Items work_items(unsigned long long rays, long long ray_tiles, int spp, int log2
     if (spp >= 8) {
         const long long by_lanes = (1ll << 20) >> log2, by_memory = (1ll << 25) / spp;
         const long long part = (ray_tiles + lp::kParts - 1) / lp::kParts;
-        const long long fine = (std::min(by_lanes, by_memory) / 64 + lp::kParts - 1) / lp::kParts;
+        const long long fine = std::min(by_lanes, by_memory) / 64 / lp::kParts;  // (rounded up, the bound would not hold)
         it.fine_units = (int)std::min(part, fine);
         // two samples per item, or one where even that leaves a lane few items
         const int least = rays * (unsigned long long)spp < (1ull << 22) ? 1 : 2;
