@@ -743,16 +743,31 @@ __global__ void points_kernel(int n, float inv_n, float* xyz, unsigned groups, f
     }
 }
 
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 hipError_t launch_points(int n, float* xyz, const float* query, long long nq, int K, int* idx, float* w,
                          hipStream_t s) {
     const float inv_n = 1.0f / (float)n;
     const float inv_r = 1.0f / sqrtf(4.0f * kPi * inv_n);
     const unsigned groups = xyz ? (unsigned)(n + 255) / 256 : 0u;
-    const unsigned all = groups + (unsigned)(query ? (nq + 255) / 256 : 0);
-    if (all == 0) return hipSuccess;
-    if (K <= 1) points_kernel<1><<<all, 256, 0, s>>>(n, inv_n, xyz, groups, inv_r, query, nq, K, idx, w);
-    else if (K <= 5) points_kernel<5><<<all, 256, 0, s>>>(n, inv_n, xyz, groups, inv_r, query, nq, K, idx, w);
-    else points_kernel<9><<<all, 256, 0, s>>>(n, inv_n, xyz, groups, inv_r, query, nq, K, idx, w);
+    const unsigned query_groups = query ? (unsigned)((nq + 255) / 256) : 0u;
+    auto launch = [&](unsigned g, unsigned qg) {
+        if (g + qg == 0) return;
+        if (K <= 1 || qg == 0) points_kernel<1><<<g + qg, 256, 0, s>>>(n, inv_n, xyz, g, inv_r, query, nq, K, idx, w);
+        else if (K <= 5) points_kernel<5><<<g + qg, 256, 0, s>>>(n, inv_n, xyz, g, inv_r, query, nq, K, idx, w);
+        else points_kernel<9><<<g + qg, 256, 0, s>>>(n, inv_n, xyz, g, inv_r, query, nq, K, idx, w);
+    };
+    // points that are queried in place (or whose buffer a result shares) are
+    // written before the queries start
+    const size_t nx = 12 * (size_t)n, nk = 4 * (size_t)nq * (size_t)K;
+    if (query_groups && (overlap(xyz, nx, query, 12 * (size_t)nq) || overlap(xyz, nx, idx, nk) || overlap(xyz, nx, w, nk))) {
+        launch(groups, 0);
+        launch(0, query_groups);
+    } else {
+        launch(groups, query_groups);
+    }
     return hipGetLastError();
 }
 
