@@ -63,6 +63,21 @@
 
 namespace lp {
 
+// Adds a light sample's term C Tr to the sample's radiance L and returns the
+// rounded product.  The adjoint multiplies scores by the radiance gathered
+// after an event, the total less the sum so far, so both must be formed alike
+// or a rounding residue is left after the last term.  Totals from the forward
+// (srad) hold fused sums; without them the recorded terms are added up, which
+// are rounded products, so a path traced again adds the same.
+template <int MODE, class PT>
+__device__ __forceinline__ f3 add_light(const PT& P, f3 C, float Tr, f3& L) {
+#pragma clang fp contract(off)
+    const f3 p = {C.x * Tr, C.y * Tr, C.z * Tr};
+    const bool rounded = MODE == kGrad && !P.srad;
+    L = rounded ? f3{L.x + p.x, L.y + p.y, L.z + p.z} : fma3(C, Tr, L);
+    return p;
+}
+
 // STATS: the work counters of `stats` are kept (a separate instantiation, so
 // the plain kernel spends no registers on them).  VIEWS: ground-truth views
 // (pinhole rays of pixel tiles) instead of light-field rays, also a separate
@@ -416,7 +431,7 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
                 if (mode == kScore) {
                     mode = kDone;
                     if (pass == 1) {  // the shadow ray's light, and the path goes on
-                        L = L + C * Tr;
+                        add_light<MODE>(P, C, Tr, L);
                         if (b != P.maxb - 1) {
                             ++b;
                             blk = 0;
@@ -632,15 +647,15 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
                             blk = 1;
                             t = 0.0f;
                         } else {
-                            L = L + C * Tr;
+                            add_light<MODE>(P, C, Tr, L);
                             after_shadow = true;
                         }
                     } else {
+                        const f3 p = add_light<MODE>(P, C, Tr, L);
                         if constexpr (MODE == kGrad)
                             if (mode == kShadow && mark < kRecords)  // the vertex's record
-                                *(float4*)((char*)P.records + (rec_at + (uint32_t)mark) * 16u) = make_float4(
-                                    C.x * Tr, C.y * Tr, C.z * Tr, __int_as_float(nrec - mark - 1));
-                        L = L + C * Tr;
+                                *(float4*)((char*)P.records + (rec_at + (uint32_t)mark) * 16u) =
+                                    make_float4(p.x, p.y, p.z, __int_as_float(nrec - mark - 1));
                         after_shadow = true;
                     }
                 } else if (ev_real) {
