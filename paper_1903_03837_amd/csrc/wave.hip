@@ -63,6 +63,13 @@
 
 namespace lp {
 
+// Orders the wave's memory accesses before and after it across its lanes.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Adds a light sample's term C Tr to the sample's radiance L and returns the
 // rounded product.  The adjoint multiplies scores by the radiance gathered
 // after an event, the total less the sum so far, so both must be formed alike
@@ -374,7 +381,10 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
         if constexpr (MODE == kGrad) {
             const int scoring = __popcll(__ballot(mode == kScore));
             if (scoring != 0 && scoring * 64 >= kScoreLanes * live) {
-                // the lanes' lists as one, 64 records at a time
+                // the lanes' lists as one, 64 records at a time (read by other
+                // lanes than wrote them, and written anew afterwards: both
+                // orders are stated, at no instruction's cost within a wave)
+                wave_fence();
                 const int mine = mode == kScore ? nrec : 0;
                 int end = mine;  // inclusive prefix sum
 #pragma unroll
@@ -428,6 +438,7 @@ __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(Tr
                         }
                     }
                 }
+                wave_fence();
                 if (mode == kScore) {
                     mode = kDone;
                     if (pass == 1) {  // the shadow ray's light, and the path goes on
