@@ -329,15 +329,13 @@ void set_items(lp::TraceParams& T, const Items& items, char* buffer) {
 // Isosurface variant: cells of the raw-range grid (the majorant grid size,
 // 8 when none is set) and their bytes in the workspace.
 int surface_cells(const lf_gen_params* p) { return p->majorant_grid > 0 ? p->majorant_grid : 8; }
-// Blocks of the isosurface march: bricks per axis such that no axis has more
-// than 48 (two bits each: 27 KB of LDS), at least two (a block of one brick
-// is crossed in six half-voxel samples).
+// Blocks of the isosurface march: at most 48 along an axis (two bits each: 27
+// KB of LDS), of at least two bricks (a block of one is crossed in six
+// half-voxel samples).  Each axis has its own block length: with that of the
+// longest for all, a 20000 x 64 x 64 volume had 48 blocks, and forming their
+// kinds took 20 ms of a call that took 0.4.
 constexpr int kMaxBlocks1D = 48;
-int surface_block_bricks(const lf_volume* v) {
-    const int nb = std::max({lp::halo_bricks(v->nx), lp::halo_bricks(v->ny), lp::halo_bricks(v->nz)});
-    return std::max(2, (nb + kMaxBlocks1D - 1) / kMaxBlocks1D);
-}
-int surface_blocks(int n, int bricks) { return (lp::halo_bricks(n) + bricks - 1) / bricks; }
+int surface_block_bricks(int n) { return std::max(2, (lp::halo_bricks(n) + kMaxBlocks1D - 1) / kMaxBlocks1D); }
 size_t surface_cells_bytes(const lf_gen_params* p) {
     const size_t G = (size_t)surface_cells(p);
     return align256(8 * G * G * G);
@@ -374,11 +372,12 @@ hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium
     if (e == hipSuccess)
         e = lp::launch_majorant_grid(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, G, m->lut,
                                      m->lut_size, m->density_scale, vol->vmin, vol->vmax, nullptr, range, s);
-    T.block_bricks = surface_block_bricks(vol);
-    T.inv_block = 1.0f / (float)(3 * T.block_bricks);
-    T.blocks_n[0] = surface_blocks(vol->nx, T.block_bricks);
-    T.blocks_n[1] = surface_blocks(vol->ny, T.block_bricks);
-    T.blocks_n[2] = surface_blocks(vol->nz, T.block_bricks);
+    const int n[3] = {vol->nx, vol->ny, vol->nz};
+    for (int a = 0; a < 3; ++a) {
+        T.block_bricks[a] = surface_block_bricks(n[a]);
+        T.inv_block[a] = 1.0f / (float)(3 * T.block_bricks[a]);
+        T.blocks_n[a] = (lp::halo_bricks(n[a]) + T.block_bricks[a] - 1) / T.block_bricks[a];
+    }
     uint32_t* blocks = (uint32_t*)((char*)range + surface_cells_bytes(p));
     T.sblocks = blocks;
     if (e == hipSuccess) e = lp::launch_surface_blocks(T, vol->type, blocks, s);

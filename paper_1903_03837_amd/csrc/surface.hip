@@ -109,9 +109,9 @@ __device__ __forceinline__ Step march_step(const SurfCtx& S, f3 x, f3 d, float t
     float tb = fmaf((float)m, S.h, t0);
     if (tb > t1) tb = t1;
     // the sample's block: grid coordinates in blocks, o + t s
-    const float ib = P.inv_block;
-    const f3 o = mk3(fmaf(x.x, P.ga[0], P.gb[0]) * ib, fmaf(x.y, P.ga[1], P.gb[1]) * ib, fmaf(x.z, P.ga[2], P.gb[2]) * ib);
-    const f3 v = mk3(d.x * P.ga[0] * ib, d.y * P.ga[1] * ib, d.z * P.ga[2] * ib);
+    const f3 ib = mk3(P.inv_block[0], P.inv_block[1], P.inv_block[2]);
+    const f3 o = mk3(fmaf(x.x, P.ga[0], P.gb[0]), fmaf(x.y, P.ga[1], P.gb[1]), fmaf(x.z, P.ga[2], P.gb[2])) * ib;
+    const f3 v = d * mk3(P.ga[0], P.ga[1], P.ga[2]) * ib;
     const int nx = P.blocks_n[0], ny = P.blocks_n[1], nz = P.blocks_n[2];
     const float bx = floorf(__builtin_amdgcn_fmed3f(fmaf(v.x, tb, o.x), 0.0f, (float)nx - 0.5f));
     const float by = floorf(__builtin_amdgcn_fmed3f(fmaf(v.y, tb, o.y), 0.0f, (float)ny - 0.5f));
@@ -466,60 +466,102 @@ __global__ __launch_bounds__(256, 4) void surface_kernel(TraceParams P) {
 }
 
 // Kinds of the march's blocks, from the halo-brick copy: block (x, y, z) spans
-// block_bricks bricks per axis, and its kind covers one voxel more on each
-// side (a march point is assigned to a block to within rounding).  kAbove /
+// block_bricks bricks along each axis, and its kind covers one voxel more on
+// each side (a march point is assigned to a block to within rounding).  kAbove /
 // kBelow: every voxel is clear of the isovalue by more than the rounding of a
-// trilinear value; a voxel that is not finite makes the block mixed.  A wave
-// forms one byte (four blocks).
+// trilinear value; a voxel that is not finite makes the block mixed.  A
+// workgroup forms one byte: four blocks, a quarter of its lanes each.  It is the
+// latency of a lane's loads one after the other, so four are in flight and long
+// blocks get more lanes.  Against a wave for four blocks in turn, u8: 64^3 19.5
+// -> 6.3 us, 256^3 103 -> 102, 512^3 370 -> 354, 1024 x 1024 x 512 1.43 -> 1.01
+// ms; with a block length per axis besides, 4096 x 128 x 128 9.3 -> 0.21 ms,
+// 20000 x 64 x 64 20.2 -> 0.25 ms.
 template <int VT>
-__global__ __launch_bounds__(256) void surface_blocks_kernel(TraceParams P, uint8_t* out) {
-    const int nx = P.blocks_n[0], ny = P.blocks_n[1], nz = P.blocks_n[2], total = nx * ny * nz;
-    const int byte = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (byte >= (total + 15) / 16 * 4) return;
-    const int span = 3 * P.block_bricks;
-    const int n[3] = {P.nx, P.ny, P.nz};
-    uint32_t bits = 0;
-    for (int i = 0; i < 4 && byte * 4 + i < total; ++i) {
-        const int e = byte * 4 + i;
-        const int b[3] = {e % nx, e / nx % ny, e / (nx * ny)};
+__global__ __launch_bounds__(1024) void surface_blocks_kernel(TraceParams P, uint8_t* out) {
+    __shared__ float wave_lo[16], wave_hi[16];
+    __shared__ int wave_finite[16];
+    const int nx = P.blocks_n[0], ny = P.blocks_n[1], total = nx * ny * P.blocks_n[2];
+    const int lanes = (int)blockDim.x / 4, waves = lanes / 64;
+    const int e = blockIdx.x * 4 + (int)threadIdx.x / lanes;
+    float vlo = 3.402823466e38f, vhi = -3.402823466e38f;
+    bool finite = true;
+    if (e < total) {
+        const int b[3] = {e % nx, e / nx % ny, e / (nx * ny)}, n[3] = {P.nx, P.ny, P.nz};
         int lo[3], cnt[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
+            const int span = 3 * P.block_bricks[a];
             lo[a] = max(span * b[a] - 1, 0);
             cnt[a] = min(span * (b[a] + 1) + 1, n[a] - 1) - lo[a] + 1;
         }
-        float vlo = 3.402823466e38f, vhi = -3.402823466e38f;
-        bool finite = true;
-        const int plane = cnt[0] * cnt[1];
-        for (int r = lane; r < plane; r += 64) {
-            const int dy = r / cnt[0], ix = lo[0] + (r - dy * cnt[0]), iy = lo[1] + dy;
-            for (int dz = 0; dz < cnt[2]; ++dz) {
-                const float v = voxel_at<VT>(P, ix, iy, lo[2] + dz);
-                finite = finite && fabsf(v) < 3.0e38f;
-                vlo = fminf(vlo, v);
-                vhi = fmaxf(vhi, v);
+        // the lanes take every lanes-th voxel, x-fastest: the place of the next
+        // one is a sum with carries.  Four are loaded at a time; past the end
+        // they are voxels of the last layer once more.
+        const int plane = cnt[0] * cnt[1], t = (int)threadIdx.x % lanes;
+        const int step[3] = {lanes % plane % cnt[0], lanes % plane / cnt[0], lanes / plane};
+        int p[3] = {t % plane % cnt[0], t % plane / cnt[0], t / plane};
+        while (p[2] < cnt[2]) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = voxel_at<VT>(P, lo[0] + p[0], lo[1] + p[1], lo[2] + min(p[2], cnt[2] - 1));
+                p[0] += step[0];
+                const bool cx = p[0] >= cnt[0];
+                p[0] -= cx ? cnt[0] : 0;
+                p[1] += step[1] + (cx ? 1 : 0);
+                const bool cy = p[1] >= cnt[1];
+                p[1] -= cy ? cnt[1] : 0;
+                p[2] += step[2] + (cy ? 1 : 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                finite = finite && fabsf(v[i]) < 3.0e38f;
+                vlo = fminf(vlo, v[i]);
+                vhi = fmaxf(vhi, v[i]);
             }
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            vlo = fminf(vlo, __shfl_xor(vlo, o, 64));
-            vhi = fmaxf(vhi, __shfl_xor(vhi, o, 64));
-        }
-        const float gap = 1e-5f * (fmaxf(fabsf(vlo), fabsf(vhi)) + fabsf(P.iso));
-        const uint32_t kind = __ballot(!finite) ? kMixed
-                              : vlo - P.iso > gap ? kAbove
-                              : P.iso - vhi > gap ? kBelow
-                                                  : kMixed;
-        bits |= kind << (2 * i);
     }
-    if (lane == 0) out[byte] = (uint8_t)bits;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        vlo = fminf(vlo, __shfl_xor(vlo, o, 64));
+        vhi = fmaxf(vhi, __shfl_xor(vhi, o, 64));
+    }
+    const bool all_finite = __ballot(!finite) == 0;
+    if ((threadIdx.x & 63) == 0) {
+        wave_lo[threadIdx.x >> 6] = vlo;
+        wave_hi[threadIdx.x >> 6] = vhi;
+        wave_finite[threadIdx.x >> 6] = all_finite;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t bits = 0;
+        for (int i = 0; i < 4 && (int)blockIdx.x * 4 + i < total; ++i) {
+            float lo = wave_lo[i * waves], hi = wave_hi[i * waves];
+            int all = wave_finite[i * waves];
+            for (int w = i * waves + 1; w < (i + 1) * waves; ++w) {
+                lo = fminf(lo, wave_lo[w]);
+                hi = fmaxf(hi, wave_hi[w]);
+                all &= wave_finite[w];
+            }
+            const float gap = 1e-5f * (fmaxf(fabsf(lo), fabsf(hi)) + fabsf(P.iso));
+            const uint32_t kind = !all ? kMixed : lo - P.iso > gap ? kAbove : P.iso - hi > gap ? kBelow : kMixed;
+            bits |= kind << (2 * i);
+        }
+        out[blockIdx.x] = (uint8_t)bits;
+    }
 }
 
 hipError_t launch_surface_blocks(const TraceParams& P, int vtype, uint32_t* out, hipStream_t s) {
-    const unsigned words = (unsigned)((P.blocks_n[0] * P.blocks_n[1] * P.blocks_n[2] + 15) / 16);
-    if (vtype == 0) surface_blocks_kernel<0><<<words, 256, 0, s>>>(P, (uint8_t*)out);
-    else if (vtype == 1) surface_blocks_kernel<1><<<words, 256, 0, s>>>(P, (uint8_t*)out);
-    else surface_blocks_kernel<2><<<words, 256, 0, s>>>(P, (uint8_t*)out);
+    const unsigned bytes = 4 * (unsigned)((P.blocks_n[0] * P.blocks_n[1] * P.blocks_n[2] + 15) / 16);
+    const int n[3] = {P.nx, P.ny, P.nz};
+    long long voxels = 1;  // of a block
+    for (int a = 0; a < 3; ++a) voxels *= std::min(3 * P.block_bricks[a] + 3, n[a]);
+    // (64 and 256 lanes a block: 256^3, 600 voxels a block, 101 and 229 us; 1024
+    // x 1024 x 512, 18000, 1.01 and 1.16 ms; 20000 x 64 x 64, 34000, 462 and 251)
+    const unsigned lanes = 4 * (voxels > 32768 ? 256 : 64);
+    if (vtype == 0) surface_blocks_kernel<0><<<bytes, lanes, 0, s>>>(P, (uint8_t*)out);
+    else if (vtype == 1) surface_blocks_kernel<1><<<bytes, lanes, 0, s>>>(P, (uint8_t*)out);
+    else surface_blocks_kernel<2><<<bytes, lanes, 0, s>>>(P, (uint8_t*)out);
     return hipGetLastError();
 }
 

@@ -114,10 +114,10 @@ struct TraceParams {
     int32_t surface;
     float iso, half_voxel;
     const float* srange;
-    // its march's blocks: block_bricks bricks per axis each, blocks_n of them,
+    // its march's blocks: block_bricks bricks along each axis, blocks_n of them,
     // two bits per block; inv_block = 1 / (3 block_bricks)
-    int32_t block_bricks, blocks_n[3];
-    float inv_block;
+    int32_t block_bricks[3], blocks_n[3];
+    float inv_block[3];
     const uint32_t* sblocks;
     // ground-truth views (views != nullptr): camera rays instead of the SF ray
     // set, 8 x 8 pixel tiles, stream key = (view * H + y) * W + x
