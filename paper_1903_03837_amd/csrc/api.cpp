@@ -336,6 +336,14 @@ int surface_cells(const lf_gen_params* p) { return p->majorant_grid > 0 ? p->maj
 // kinds took 20 ms of a call that took 0.4.
 constexpr int kMaxBlocks1D = 48;
 int surface_block_bricks(int n) { return std::max(2, (lp::halo_bricks(n) + kMaxBlocks1D - 1) / kMaxBlocks1D); }
+void set_surface_blocks(lp::TraceParams& T, const lf_volume* v) {
+    const int n[3] = {v->nx, v->ny, v->nz};
+    for (int a = 0; a < 3; ++a) {
+        T.block_bricks[a] = surface_block_bricks(n[a]);
+        T.inv_block[a] = 1.0f / (float)(3 * T.block_bricks[a]);
+        T.blocks_n[a] = (lp::halo_bricks(n[a]) + T.block_bricks[a] - 1) / T.block_bricks[a];
+    }
+}
 size_t surface_cells_bytes(const lf_gen_params* p) {
     const size_t G = (size_t)surface_cells(p);
     return align256(8 * G * G * G);
@@ -372,12 +380,7 @@ hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium
     if (e == hipSuccess)
         e = lp::launch_majorant_grid(vol->data, vol->type, vol->brick, vol->nx, vol->ny, vol->nz, G, m->lut,
                                      m->lut_size, m->density_scale, vol->vmin, vol->vmax, nullptr, range, s);
-    const int n[3] = {vol->nx, vol->ny, vol->nz};
-    for (int a = 0; a < 3; ++a) {
-        T.block_bricks[a] = surface_block_bricks(n[a]);
-        T.inv_block[a] = 1.0f / (float)(3 * T.block_bricks[a]);
-        T.blocks_n[a] = (lp::halo_bricks(n[a]) + T.block_bricks[a] - 1) / T.block_bricks[a];
-    }
+    set_surface_blocks(T, vol);
     uint32_t* blocks = (uint32_t*)((char*)range + surface_cells_bytes(p));
     T.sblocks = blocks;
     if (e == hipSuccess) e = lp::launch_surface_blocks(T, vol->type, blocks, s);

@@ -45,6 +45,13 @@ struct SurfCtx {
 };
 
 enum : uint32_t { kMixed = 0, kAbove = 1, kBelow = 2 };
+// Voxels from here on count as not finite.
+constexpr float kLargeVoxel = 3.0e38f;
+// Kind of a block whose voxels lie in [lo, hi].
+__device__ __forceinline__ uint32_t block_kind(float lo, float hi, bool finite, float iso) {
+    const float gap = 1e-5f * (fmaxf(fabsf(lo), fabsf(hi)) + fabsf(iso));
+    return !finite ? kMixed : lo - iso > gap ? kAbove : iso - hi > gap ? kBelow : kMixed;
+}
 
 template <int VT>
 __device__ __forceinline__ float field(const SurfCtx& S, f3 y) {
@@ -515,7 +522,7 @@ __global__ __launch_bounds__(1024) void surface_blocks_kernel(TraceParams P, uin
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                finite = finite && fabsf(v[i]) < 3.0e38f;
+                finite = finite && fabsf(v[i]) < kLargeVoxel;
                 vlo = fminf(vlo, v[i]);
                 vhi = fmaxf(vhi, v[i]);
             }
@@ -543,9 +550,7 @@ __global__ __launch_bounds__(1024) void surface_blocks_kernel(TraceParams P, uin
                 hi = fmaxf(hi, wave_hi[w]);
                 all &= wave_finite[w];
             }
-            const float gap = 1e-5f * (fmaxf(fabsf(lo), fabsf(hi)) + fabsf(P.iso));
-            const uint32_t kind = !all ? kMixed : lo - P.iso > gap ? kAbove : P.iso - hi > gap ? kBelow : kMixed;
-            bits |= kind << (2 * i);
+            bits |= block_kind(lo, hi, all, P.iso) << (2 * i);
         }
         out[blockIdx.x] = (uint8_t)bits;
     }
