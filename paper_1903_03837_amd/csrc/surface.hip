@@ -45,8 +45,9 @@ struct SurfCtx {
 };
 
 enum : uint32_t { kMixed = 0, kAbove = 1, kBelow = 2 };
-// Voxels from here on count as not finite.
-constexpr float kLargeVoxel = 3.0e38f;
+// Voxels from here on count as not finite (the differences that interpolation
+// forms of smaller ones are finite).
+constexpr float kLargeVoxel = 1.7e38f;
 // Kind of a block whose voxels lie in [lo, hi].
 __device__ __forceinline__ uint32_t block_kind(float lo, float hi, bool finite, float iso) {
     const float gap = 1e-5f * (fmaxf(fabsf(lo), fabsf(hi)) + fabsf(iso));

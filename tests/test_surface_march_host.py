@@ -109,6 +109,17 @@ def test_voxels_that_are_not_finite(probe, spoil):
         assert met > 5000 and differ == 0
 
 
+def test_voxels_whose_differences_overflow(probe):
+    """2e38 and -2e38 lie on one side of -2.5e38, but interpolating between them
+    gives infinities and NaN, which a march that fetches meets."""
+    def huge(x, y, z):
+        return np.where((x // 3 + y // 4 + z // 5) % 3 == 0, -2e38, 2e38)
+
+    for iso in (-2.5e38, 2.5e38):
+        met, _, differ, _, _ = march(probe, (60, 50, 51), huge, iso, F32, spoil=2e38)
+        assert met > 5000 and differ == 0
+
+
 # rows of bricks (nby x nbz) below and above 2^24, the longest axes, and copies
 # of nearly 2^32 voxels
 @pytest.mark.parametrize("dims", [(2, 2, 2), (65535, 2, 2), (2, 65535, 2), (2, 2, 65535), (2, 30000, 5000),
