@@ -332,8 +332,8 @@ int surface_cells(const lf_gen_params* p) { return p->majorant_grid > 0 ? p->maj
 // Blocks of the isosurface march: at most 48 along an axis (two bits each: 27
 // KB of LDS), of at least two bricks (a block of one is crossed in six
 // half-voxel samples).  Each axis has its own block length: with that of the
-// longest for all, a 20000 x 64 x 64 volume had 48 blocks, and forming their
-// kinds took 20 ms of a call that took 0.4.
+// longest for all, a 6000 x 500 x 100 volume had 192 blocks, and forming their
+// kinds took 27 ms of a call that took 1.
 constexpr int kMaxBlocks1D = 48;
 int surface_block_bricks(int n) { return std::max(2, (lp::halo_bricks(n) + kMaxBlocks1D - 1) / kMaxBlocks1D); }
 void set_surface_blocks(lp::TraceParams& T, const lf_volume* v) {
@@ -343,6 +343,21 @@ void set_surface_blocks(lp::TraceParams& T, const lf_volume* v) {
         T.inv_block[a] = 1.0f / (float)(3 * T.block_bricks[a]);
         T.blocks_n[a] = (lp::halo_bricks(n[a]) + T.block_bricks[a] - 1) / T.block_bricks[a];
     }
+}
+long long surface_block_words(const lp::TraceParams& T) {
+    return ((long long)T.blocks_n[0] * T.blocks_n[1] * T.blocks_n[2] + 15) / 16;
+}
+// Whether the blocks' kinds are formed (else all are mixed, and every sample is
+// fetched): that is a pass over the volume, and what it saves are samples of
+// rays, which cross a long volume along its short axes.  With and without, 16 x
+// 16 rays of one sample and 512 x 512 of four: 2048 x 128 x 128 0.42 and 0.36,
+// 1.65 and 1.84 ms; 4096 x 128 x 128 0.63 and 0.47, 1.86 and 1.88; 8192 x 128 x
+// 128 1.14 and 0.58, 2.42 and 2.10; 2048 x 2048 x 16 0.67 and 0.72, 1.62 and
+// 2.26.
+bool blocks_pay(const lf_volume* v) {
+    int n[3] = {v->nx, v->ny, v->nz};
+    std::sort(n, n + 3);
+    return n[2] <= 24 * n[1];
 }
 size_t surface_cells_bytes(const lf_gen_params* p) {
     const size_t G = (size_t)surface_cells(p);
@@ -383,7 +398,9 @@ hipError_t run_surface(lp::TraceParams& T, const lf_volume* vol, const lf_medium
     set_surface_blocks(T, vol);
     uint32_t* blocks = (uint32_t*)((char*)range + surface_cells_bytes(p));
     T.sblocks = blocks;
-    if (e == hipSuccess) e = lp::launch_surface_blocks(T, vol->type, blocks, s);
+    if (e == hipSuccess)
+        e = blocks_pay(vol) ? lp::launch_surface_blocks(T, vol->type, blocks, s)
+                            : lp::launch_zero((float*)blocks, surface_block_words(T), s);  // (all mixed)
     if (e == hipSuccess) e = lp::launch_surface(T, vol->type, s);
     if (e == hipSuccess) e = lp::launch_combine_parts(T, s);
     return e;

@@ -478,19 +478,17 @@ __global__ __launch_bounds__(256, 4) void surface_kernel(TraceParams P) {
 // each side (a march point is assigned to a block to within rounding).  kAbove /
 // kBelow: every voxel is clear of the isovalue by more than the rounding of a
 // trilinear value; a voxel that is not finite makes the block mixed.  A
-// workgroup forms one byte: four blocks, a quarter of its lanes each.  It is the
-// latency of a lane's loads one after the other, so four are in flight and long
-// blocks get more lanes.  Against a wave for four blocks in turn, u8: 64^3 19.5
-// -> 6.3 us, 256^3 103 -> 102, 512^3 370 -> 354, 1024 x 1024 x 512 1.43 -> 1.01
-// ms; with a block length per axis besides, 4096 x 128 x 128 9.3 -> 0.21 ms,
-// 20000 x 64 x 64 20.2 -> 0.25 ms.
+// workgroup forms one byte: four blocks, a wave each.  It is the latency of a
+// lane's loads one after the other, so four are in flight.  Against a wave for
+// four blocks in turn, u8: 64^3 19.8 -> 6.3 us, 256^3 103 -> 102, 512^3 375 ->
+// 354, 1024 x 1024 x 512 1.43 -> 1.02 ms; with a block length per axis besides,
+// 2048 x 128 x 128 1.53 -> 0.11, 6000 x 500 x 100 27.1 -> 0.78 ms.  (Four waves a
+// block: 256^3 236 us, 6000 x 500 x 100 0.75 ms.)
 template <int VT>
-__global__ __launch_bounds__(1024) void surface_blocks_kernel(TraceParams P, uint8_t* out) {
-    __shared__ float wave_lo[16], wave_hi[16];
-    __shared__ int wave_finite[16];
+__global__ __launch_bounds__(256) void surface_blocks_kernel(TraceParams P, uint8_t* out) {
+    __shared__ uint32_t kinds[4];
     const int nx = P.blocks_n[0], ny = P.blocks_n[1], total = nx * ny * P.blocks_n[2];
-    const int lanes = (int)blockDim.x / 4, waves = lanes / 64;
-    const int e = blockIdx.x * 4 + (int)threadIdx.x / lanes;
+    const int wave = (int)threadIdx.x >> 6, lane = threadIdx.x & 63, e = (int)blockIdx.x * 4 + wave;
     float vlo = 3.402823466e38f, vhi = -3.402823466e38f;
     bool finite = true;
     if (e < total) {
@@ -502,12 +500,12 @@ __global__ __launch_bounds__(1024) void surface_blocks_kernel(TraceParams P, uin
             lo[a] = max(span * b[a] - 1, 0);
             cnt[a] = min(span * (b[a] + 1) + 1, n[a] - 1) - lo[a] + 1;
         }
-        // the lanes take every lanes-th voxel, x-fastest: the place of the next
-        // one is a sum with carries.  Four are loaded at a time; past the end
-        // they are voxels of the last layer once more.
-        const int plane = cnt[0] * cnt[1], t = (int)threadIdx.x % lanes;
-        const int step[3] = {lanes % plane % cnt[0], lanes % plane / cnt[0], lanes / plane};
-        int p[3] = {t % plane % cnt[0], t % plane / cnt[0], t / plane};
+        // a lane takes every 64th voxel, x-fastest: the place of the next one is
+        // a sum with carries.  Past the end they are voxels of the last layer
+        // once more.
+        const int plane = cnt[0] * cnt[1];
+        const int step[3] = {64 % plane % cnt[0], 64 % plane / cnt[0], 64 / plane};
+        int p[3] = {lane % plane % cnt[0], lane % plane / cnt[0], lane / plane};
         while (p[2] < cnt[2]) {
             float v[4];
 #pragma unroll
@@ -535,39 +533,16 @@ __global__ __launch_bounds__(1024) void surface_blocks_kernel(TraceParams P, uin
         vhi = fmaxf(vhi, __shfl_xor(vhi, o, 64));
     }
     const bool all_finite = __ballot(!finite) == 0;
-    if ((threadIdx.x & 63) == 0) {
-        wave_lo[threadIdx.x >> 6] = vlo;
-        wave_hi[threadIdx.x >> 6] = vhi;
-        wave_finite[threadIdx.x >> 6] = all_finite;
-    }
+    if (lane == 0) kinds[wave] = e < total ? block_kind(vlo, vhi, all_finite, P.iso) : kMixed;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t bits = 0;
-        for (int i = 0; i < 4 && (int)blockIdx.x * 4 + i < total; ++i) {
-            float lo = wave_lo[i * waves], hi = wave_hi[i * waves];
-            int all = wave_finite[i * waves];
-            for (int w = i * waves + 1; w < (i + 1) * waves; ++w) {
-                lo = fminf(lo, wave_lo[w]);
-                hi = fmaxf(hi, wave_hi[w]);
-                all &= wave_finite[w];
-            }
-            bits |= block_kind(lo, hi, all, P.iso) << (2 * i);
-        }
-        out[blockIdx.x] = (uint8_t)bits;
-    }
+    if (threadIdx.x == 0) out[blockIdx.x] = (uint8_t)(kinds[0] | kinds[1] << 2 | kinds[2] << 4 | kinds[3] << 6);
 }
 
 hipError_t launch_surface_blocks(const TraceParams& P, int vtype, uint32_t* out, hipStream_t s) {
     const unsigned bytes = 4 * (unsigned)((P.blocks_n[0] * P.blocks_n[1] * P.blocks_n[2] + 15) / 16);
-    const int n[3] = {P.nx, P.ny, P.nz};
-    long long voxels = 1;  // of a block
-    for (int a = 0; a < 3; ++a) voxels *= std::min(3 * P.block_bricks[a] + 3, n[a]);
-    // (64 and 256 lanes a block: 256^3, 600 voxels a block, 101 and 229 us; 1024
-    // x 1024 x 512, 18000, 1.01 and 1.16 ms; 20000 x 64 x 64, 34000, 462 and 251)
-    const unsigned lanes = 4 * (voxels > 32768 ? 256 : 64);
-    if (vtype == 0) surface_blocks_kernel<0><<<bytes, lanes, 0, s>>>(P, (uint8_t*)out);
-    else if (vtype == 1) surface_blocks_kernel<1><<<bytes, lanes, 0, s>>>(P, (uint8_t*)out);
-    else surface_blocks_kernel<2><<<bytes, lanes, 0, s>>>(P, (uint8_t*)out);
+    if (vtype == 0) surface_blocks_kernel<0><<<bytes, 256, 0, s>>>(P, (uint8_t*)out);
+    else if (vtype == 1) surface_blocks_kernel<1><<<bytes, 256, 0, s>>>(P, (uint8_t*)out);
+    else surface_blocks_kernel<2><<<bytes, 256, 0, s>>>(P, (uint8_t*)out);
     return hipGetLastError();
 }
 

@@ -50,11 +50,12 @@ def test_long_volumes_match_oracle(lp, orc, dims, box, vtype):
     assert err <= 1e-3  # the bar of the isosurface tests
 
 
-@pytest.mark.parametrize("dims", [(20000, 64, 64), (64, 64, 20000), (4096, 128, 128)])
+@pytest.mark.parametrize("dims", [(20000, 64, 64), (64, 64, 20000), (4096, 128, 128), (2048, 128, 128)])
 def test_time_of_a_small_field(lp, dims):
     """A small field's time is passes over the volume, in the isosurface variant
-    as in the volume tracer: the former reads it once more, with a margin of two
-    voxels around blocks of six or more, (8/6)^2 times where two axes are short."""
+    as in the volume tracer.  The former reads it at most once more, with a margin
+    of two voxels around blocks of six or more: (8/6)^2 times where two axes are
+    short."""
     n = dims[0] * dims[1] * dims[2]
     sc = scene((8, 8, 8), S.U16, (1.0, 1.0, 1.0), (2.0, 2.0, 2.0), M=8, N=9, spp=1)
     vol, med, light, prm, _ = lp.device_scene(sc)
