@@ -132,8 +132,8 @@ typedef struct {
  * lf_generate writes the radiance of every sample of every generated ray
  * at ((i*N + j)*spp + s)*3 (texels i == j are not written, and of a ray
  * that misses the volume box in every sample only the last sample is);
- * lf_generate_backward reads it instead of tracing each sample a first
- * time.  It must come from lf_generate with the same parameters and medium
+ * lf_generate_backward reads it instead of recording a path's events until
+ * its radiance is known.  It must come from lf_generate with the same parameters and medium
  * and sample == NULL.
  * waves_per_simd: 0, 3 or 4 (else LF_E_ARG).  A performance hint of earlier
  * versions, whose forward kernels could be budgeted for three resident waves
@@ -197,7 +197,11 @@ int lf_points(int32_t n, float* xyz_out, const float* query, int64_t nq, int32_t
  * R_spp = 4 when spp >= 32, 2 when spp >= 16, else 1; R_rays = 4 when
  * M*N < 1572864, 2 when M*N < 12582912, else 1; and R = 1 whenever
  * M*N*spp > 2^31 (the ranges are work items of their own, for load balance;
- * the workspace then holds their sums).
+ * the workspace then holds their sums).  From 8 to 65536 samples per ray the
+ * workspace also holds every sample of up to 2^20 / R rays, the last ones to be
+ * traced, which are split further: 12 bytes each, at most 2^25 of them (403
+ * MB); when these are all rays there are no range sums.  The mean's order of
+ * summation is the same.
  *   eval:   medium evaluated.   sample: NULL, or the medium that decides
  *   collisions (frozen sampling: the path is importance-weighted from sample
  *   to eval; used for finite-difference checks of the adjoint).

@@ -393,7 +393,7 @@ def generate_backward(vol: Volume, med: Medium, light: Light, prm: GenParams, d_
                       sample_radiance: Optional[torch.Tensor] = None):
     """lf_generate_backward: (d_lut [L,4], d_scale [1]) for d(loss)/d(Lhat).
     sample_radiance: None, or the per-sample radiance that generate() kept
-    with the same parameters and medium (the first replay pass is skipped)."""
+    with the same parameters and medium (scores are formed while tracing)."""
     d_lf = d_lf.contiguous().float()
     _need(d_lf, prm.rows * prm.N * 3, torch.float32, "d_lf")
     d_lut = torch.empty_like(med.lut)
@@ -487,7 +487,8 @@ class LightFieldFn(torch.autograd.Function):
     """Lhat = generate(LUT, density scale); backward by path replay
     (lf_generate_backward).  `scale` is a 0-d float tensor on the CPU.  With
     keep_samples the forward keeps every sample's radiance (rows x N x spp x
-    12 bytes) so that the backward traces each sample once instead of twice."""
+    12 bytes) so that the backward traces every sample once, also those with
+    more events than it records."""
 
     @staticmethod
     def forward(ctx, lut, scale, vol, light, prm, keep_samples=False):

@@ -89,20 +89,21 @@ constexpr size_t kCtrBytes = 4 * kCtrStride * lp::kParts;
 
 // Work items of a forward whose mean sums 2^log2 ranges of a ray's samples.  A
 // lane walks its item's samples one after the other, so when the queue runs
-// dry most lanes still hold part of an item, and the longest sets the time:
-// with 32-sample items (256^3, N = 2048, 64 spp) the last 12 of 71 ms went by
-// after the queue was dry.  So the last rays of the queue are split down to
+// dry most lanes still hold part of an item, and the longest sets the time
+// (a sixth of it with 32-sample items in a dense scene).  So the last rays of the queue are split down to
 // two samples per item (one where the launch is small), their samples kept
 // and summed by a second kernel in the same order (same bits).  They make up
-// four ordinary items of every lane of the full grid (2^18 lanes), enough to
+// four ordinary items of every lane of the MI355X's full grid (2^18), enough to
 // fill the gaps that the longest ordinary items leave, and at most 2^25
 // samples (403 MB): from 65537 samples per ray on, one tile of each part would
 // pass that, and nothing is split.  Below 8 samples per ray there is little to
 // split.
-// Measured: 256^3 step 58.0 -> 53.0 ms (two items per lane instead of four
-// 55.5, eight 53.4; one or four samples per item 53.5), views at 256 spp 17.1
-// -> 15.5 ms, 128^3 training pass 18.7 -> 18.1 ms; 64^3, N = 256, 16 spp 1.18
-// -> 0.50 ms with the counters below (two samples per item 0.63).
+// Measured without and with it on the synthetic phantoms at their default
+// settings: 64^3, N = 256, 16 spp 0.88 and 0.43 ms (two samples per item 0.50);
+// isosurface of the 256^3 one, N = 1024, 16 spp 8.6 and 5.3 (two items per lane
+// 7.6, eight 5.4); its field, N = 2048, 64 spp 8.67 and 8.55 (two 8.6, eight 9.0;
+// one sample per item 8.9, four 8.5); 128^3 training pass 9.3 and 9.1; but two
+// 480 x 270 views at 256 spp, whose pixels end alike, 2.24 and 2.36.
 struct Items {
     int log2 = 0;                       // ranges per ray
     int fine_units = 0, fine_log2 = 0;  // ray tiles of each part split finely, their items per ray

@@ -106,9 +106,9 @@ struct Footprint {
 // voxels, and one more on each side, are clear of the isovalue by more than
 // the rounding of positions and interpolation.  (In mixed blocks one sample a
 // step: fetching two or four together took 16 and 36 % longer, their waves
-// being kept busy by the other lanes' steps.)  256^3 u16, N = 1024, 16 spp:
-// 45.4 ms as nested loops of one ray per lane, 18.6 with the blocks and
-// without bisecting visibility rays, 5.8 as a state machine (an eighth of the
+// being kept busy by the other lanes' steps.)  256^3 u16 phantom, N = 1024, 16
+// spp: 45 ms as nested loops of one ray per lane, 18.6 with the blocks and
+// without bisecting visibility rays, 5.7 as a state machine (an eighth of the
 // lanes were active before it).
 enum class Step { kOn, kMiss, kCross };
 template <int VT>

@@ -173,13 +173,15 @@ enum : int {
 // Records a lane can keep for scoring (adjoint; 64, the bits of a mask: 97 % of
 // the events of a 128^3 training pass lie in paths that fit, two thirds of
 // a 256^3 one with eight bounces), and the lanes of 64 live ones that wait
-// before a wave scores (4, 8 and 32: 3 % more, 1 % more and 3 % more time).
+// before a wave scores (dense adjoint of the 128^3 blobs, N = 1024, 32 spp: 5.79
+// ms; 8 lanes 5.85, 32 lanes 6.10).
 constexpr int kRecords = 64;
 constexpr int kScoreLanes = 16;
 // Divisor of a point that is not on its segment (the bits of a NaN that no
 // arithmetic returns).
 constexpr uint32_t kNoPoint = 0x7fc0a11eu;
-// Workgroups that have records: a full grid (256 CUs, three each).
+// Workgroups that have records: a full grid of the MI355X (256 CUs, three
+// each), so that the workspace has a fixed bound.  The launch never exceeds it.
 constexpr int kRecordGroups = 768;
 // A further tracking pass runs while at least this many lanes of a wave are
 // still tracking a segment.
@@ -239,9 +241,10 @@ struct Tile {
 // part's counter, one atomic each.  A wave that finds a part taken looks at
 // all counters with one load before it tries another part: with every wave
 // trying every part in turn, and the counters in one cache line, the atomics
-// held small launches (10 us and more per refill): 64^3 volume, N = 256, 16
-// spp 777 -> 480-500 us with the counters a line apart, the first tile by
-// position and one look at all counters.
+// held small launches (10 us and more per refill).  With the counters in one
+// line and a line apart: 64^3 blobs, N = 256, 16 spp 0.62 and 0.43 ms; two 480 x
+// 270 views of the 256^3 phantom at 256 spp 3.9 and 2.4 ms; its field, N = 2048,
+// 64 spp 10.6 and 8.6 ms.
 __device__ __forceinline__ bool next_tile(unsigned int* ctr, int stride, const Queue& Q, int home, int idx, bool& begun,
                                           unsigned& dry, Tile& T) {
     const int lane = threadIdx.x & 63;
@@ -301,11 +304,12 @@ struct Counters {
 // never crosses a cache line; it is aligned to the voxel size only (the
 // types below), which global loads allow.  The fetch was bound by its load
 // and address instructions: 16 loads per pair of points, each with a 64-bit
-// address of its own, against 8 now at fixed offsets from one address
-// (256^3 u16 phantom, N = 2048, 64 spp with lookups and adjoint 69.2 -> 60.7
-// ms; 270 x 480 views of it at 256 spp 21.3 -> 19.4 ms; 512^3, N = 32768 at
-// 3 waves per SIMD, where HBM bounds it, 204.8 -> 196.0 ms per 2048 rows;
-// isosurface, N = 1024 44.8 -> 39.7 ms).
+// address of its own, against 8 now at fixed offsets from one address.  On the
+// synthetic phantoms at their default settings: 256^3 u16, N = 2048, 64 spp
+// 10.0 -> 9.5 ms; 512^3, N = 32768, 16 spp, 2048 rows 292 -> 251 ms (278 -> 265
+// where the kernel then had 3 waves per SIMD); isosurface of the 256^3 one, N =
+// 1024, 16 spp 52.2 -> 44.8 ms; 128^3 f32 training pass 14.3 -> 13.9 ms; two 480
+// x 270 views at 256 spp 2.4 ms with either.
 typedef uint16_t u16_at1 __attribute__((aligned(1)));
 typedef uint32_t u32_at2 __attribute__((aligned(2)));
 typedef float f32x2_at4 __attribute__((ext_vector_type(2), aligned(4)));

@@ -52,10 +52,11 @@
 // again with its radiance known, its flights scored as they happen, and so is
 // every sample whose radiance the forward kept; a shadow ray's steps are then
 // recorded in the same way, and traced again if they are too many.
-// The tracing bounds it, as it does the forward.  128^3 f32, N = 1024, 32 spp
-// (10 events per sample, 7.5 of them in shadow rays), the training step:
-// 19.2 ms when every sample was traced a second time and its shadow rays a
-// third, 18.1 when each lane scored its own list (a quarter of the lanes
+// The tracing bounds it, as it does the forward.  Dense adjoint of the 128^3
+// blobs, N = 1024, 32 spp: 7.9 ms when every sample was traced a second time and
+// its shadow rays a third, 5.8 now.  The training step of a denser scene of
+// these sizes (10 events per sample, 7.5 of them in shadow rays): 19.2 ms
+// before, 18.1 when each lane scored its own list (a quarter of the lanes
 // busy), 15.3 when the lists are shared, 14.4 at three waves per SIMD; 11.6
 // with the scoring left out.  Several copies of the LDS sums against
 // conflicting atomics: no difference.
@@ -89,12 +90,14 @@ __device__ __forceinline__ f3 add_light(const PT& P, f3 C, float Tr, f3& L) {
 // the plain kernel spends no registers on them).  VIEWS: ground-truth views
 // (pinhole rays of pixel tiles) instead of light-field rays, also a separate
 // instantiation so that the light-field kernel carries none of its code.
-// Registers are budgeted for four resident waves per SIMD (128 VGPRs; frozen
-// sampling spills a few values), the adjoint's for three (166, where four
-// spilled 33 values: the training step took 15.3 instead of 14.4 ms).  Other budgets measured: five
-// waves (96) take the 256^3 u16 step from 58 to 71 ms and views from 17.3 to
-// 20.6 ms; three resident waves take the 512^3 field at N = 32768 from 152 to
-// 167 ms per 2048 rows.
+// Registers are budgeted for four resident waves per SIMD (128 VGPRs; the plain
+// forward spills 9 to 13 values by voxel type, the views 6 to 8, frozen sampling
+// 15 or 16, the instantiations with work counts 26 to 34), the adjoint's for
+// three (166 or 168, none spilled).  Other budgets, on the synthetic phantoms at
+// their default settings: 256^3, N = 2048, 64 spp 8.5 ms, with five waves (96
+// VGPRs) 11.4, with three 9.2; two 480 x 270 views of it at 256 spp 2.4, 3.3 and
+// 2.3; 512^3, N = 32768, 2048 rows 249, 307 and 248; the 128^3 dense adjoint 5.8
+// ms, 7.8 with four waves.
 template <int VT, int MODE, bool STATS, bool VIEWS>
 __global__ __launch_bounds__(256, MODE == kGrad ? 3 : 4) void gen_wave_kernel(TraceParams P) {
     // LDS: cell majorants and their reciprocals (first, so that the grid walk's
